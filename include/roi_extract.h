@@ -234,6 +234,10 @@ re_status_t roi_extract_zero_grad(const re_level_t *grad_levels, int32_t num_lev
  *           requested but not eligible.  With a NaN or infinity in grad_out the
  *           scatter follows the definition exactly, while the gather may also put it
  *           on untapped pixels of the rows the RoI's bin row touches in a quadrant;
+ *           With a sampling ratio other than 2 on the 7x7 and 14x14 grids,
+ *           RE_BWD_AUTO sums per tile as well when `plan` is given (RE_BWD_GATHER
+ *           stays limited to 2): the result is the scatter's, also for RoIs whose
+ *           roi_levels differ from the plan's and for non-finite values;
  *   other arguments as roi_align_fwd. */
 re_status_t roi_align_bwd(const void *grad_out, int32_t grad_out_dtype,
                           const float *rois, int64_t num_rois, const int32_t *roi_levels,

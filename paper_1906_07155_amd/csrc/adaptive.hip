@@ -1,0 +1,864 @@
+// adaptive.hip -- RoIAlign with any sampling ratio on the 7x7 and 14x14 grids: the
+// adaptive grid (sampling_ratio 0: ceil(bin) samples per bin and axis) and fixed ratios
+// other than 2, on channels-last levels (forward) and on any levels the tile gather
+// addresses (backward).
+//
+// The sample positions of a RoI are separable whatever their number, so its output is
+//     out[ph][pw] = 1/count * sum_y sum_x Wy[ph][y] * Wx[pw][x] * F[y][x]
+// over the pixel rows y and columns x its samples tap, Wy and Wx the summed bilinear
+// weights of the bin's samples.  The number of samples then only enters the weights: the
+// kernels load (or write) every footprint pixel once, as the two-samples kernels do, and
+// not once per sample and corner.
+//
+//   fwd_any_kernel         (RoI, slice of channels) per workgroup, lanes over channels
+//   bwd_gather_any_kernel  the tile gather: (bin-tile, 64 channels) per workgroup
+//   bwd_stray_kernel       scatter of the RoIs whose level is not the plan's (normally
+//                          none): the tile lists do not hold them
+//
+// Batch of 3 x 171 RoIs, 256 binary32 channels, 608 x 1056 images, adaptive grid, against
+// one thread per output element with four taps (atomics) per sample:
+//   forward 618 -> 44 us, backward 24 (clearing) + 9996 -> 58 + 4 us (stray pass).
+#include <algorithm>
+
+#include "gather.hpp"
+
+namespace rex {
+
+constexpr int kAnyGrid = kGridCap;   // samples per bin and axis at most (RE_MAX_SAMPLING)
+
+// Position of sample i of bin p after the cut and the clamp: -2 marks a sample off the
+// map, anything else is in [0, size - 1] and its taps are (int)v and, unless that is the
+// last pixel, the next one with weight v - (int)v (the steps of axis_tap).
+__device__ __forceinline__ float any_position(const Axis &a, int p, int i, int size) {
+    const float t1 = static_cast<float>(p) * a.bin;
+    const float t2 = a.start + t1;
+    const float t3 = static_cast<float>(i) + 0.5f;
+    const float t4 = t3 * a.bin;
+    const float t5 = t4 / static_cast<float>(a.grid);
+    float v = t2 + t5;
+    if (v < -1.0f || v > static_cast<float>(size)) return -2.0f;
+    v = fmaxf(v, 0.0f);
+    return static_cast<int>(v) >= size - 1 ? static_cast<float>(size - 1) : v;
+}
+
+// Summed weight the samples of bin p put on pixel X of the axis, and whether any of them
+// taps it (also with weight zero).  pos holds the bin's positions.  Only samples within a
+// pixel of X can tap it, and the raw positions are evenly spaced, so the loop runs over
+// their index range, widened by one for rounding; a box without extent takes all samples.
+__device__ __forceinline__ float any_weight(const float *pos, const Axis &a, int p, int X, int size,
+                                            bool &hit) {
+    const float g = static_cast<float>(a.grid);
+    int i0 = 0, i1 = a.grid - 1;
+    if (a.bin > 0.0f) {
+        const float inv = g * __builtin_amdgcn_rcpf(a.bin);
+        const float rel = (static_cast<float>(X) - a.start) - static_cast<float>(p) * a.bin;
+        const float lo = (rel - 1.0f) * inv - 1.5f;   // floor - 1 of the first index
+        const float hi = (rel + 1.0f) * inv + 0.5f;   // ceil + 1 of the last
+        if (lo > 0.0f) i0 = static_cast<int>(fminf(lo, g));
+        if (hi < g - 1.0f) i1 = static_cast<int>(fmaxf(hi, -1.0f));
+    }
+    float w = 0.0f;
+    hit = false;
+#pragma unroll 1
+    for (int i = i0; i <= i1; ++i) {
+        const float v = pos[i];
+        const int l = static_cast<int>(v);
+        const float f = v - static_cast<float>(l);
+        const bool a0 = v >= 0.0f && l == X;
+        const bool a1 = v >= 0.0f && l + 1 == X && l < size - 1;
+        w += a0 ? 1.0f - f : 0.0f;
+        w += a1 ? f : 0.0f;
+        hit = hit || a0 || a1;
+    }
+    return w;
+}
+
+// Positions of every sample of both axes into pos ([bin][sample] of the rows, then of the
+// columns at kAnyGrid * P), by the whole workgroup.
+template <int P>
+__device__ __forceinline__ void any_positions(const Axis &ay, const Axis &ax, int H, int W,
+                                              float *pos) {
+    const int ny = P * ay.grid, n = ny + P * ax.grid;
+    for (int e = threadIdx.x; e < n; e += 256) {
+        const bool row = e < ny;
+        const int u = row ? e : e - ny;
+        const int g = row ? ay.grid : ax.grid;
+        const int p = small_div_exact(u, g);
+        Axis a;
+        a.start = row ? ay.start : ax.start;
+        a.bin = row ? ay.bin : ax.bin;
+        a.grid = g;
+        pos[(row ? 0 : kAnyGrid * P) + u] = any_position(a, p, u - p * g, row ? H : W);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Forward
+// ---------------------------------------------------------------------------
+//
+// As the two-samples kernel (fwd.hip): wave w owns bin rows [w * RPW, (w + 1) * RPW) and
+// loads the pixel rows they tap times the RoI's columns, in chunks of CX columns with D
+// units (chunk, row) in flight; each row is weighted into the wave's bin rows, and at the
+// end of a chunk its columns are reduced into the bin columns that tap them.  Samples are
+// at most a pixel apart (a capped grid aside), so the tapped rows and columns are runs.
+// RoIs of more than kAnyCols columns or, per wave, kAnyRows rows are
+// walked in panels of that size (a box may span the whole map), each with its own weights.
+constexpr int kAnyCols = 64;
+constexpr int kAnyRows = 32;
+
+template <typename T, int CPL>
+struct AnyPix {
+    static constexpr int W = (static_cast<int>(sizeof(T)) * CPL + 3) / 4;
+    uint32_t w[W];
+};
+
+template <typename T, int CPL>
+__device__ __forceinline__ void any_load(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff,
+                                         AnyPix<T, CPL> &p) {
+    static_assert(sizeof(T) * CPL <= 4, "one 32-bit register per lane and pixel");
+    if constexpr (sizeof(T) * CPL == 4) p.w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0);
+    else p.w[0] = __builtin_amdgcn_raw_buffer_load_b16(r, off, soff, 0);
+}
+
+template <typename T, int CPL>
+__device__ __forceinline__ float any_value(const AnyPix<T, CPL> &p, int j) {
+    if constexpr (sizeof(T) == 4) return __uint_as_float(p.w[0]);
+    else if constexpr (CPL == 1) return __uint_as_float(p.w[0] << 16);
+    else return __uint_as_float(j == 0 ? (p.w[0] << 16) : (p.w[0] & 0xffff0000u));
+}
+
+template <int P, int CHK>
+struct AnyFwdSmem {
+    float pos[2 * P * kAnyGrid];
+    __align__(16) float wx[P][kAnyCols];
+    __align__(16) float wy[4][kAnyRows][4];   // [wave][row][bin row of the wave]
+    __align__(16) uint32_t xoff[kAnyCols];    // byte offsets of the panel's columns
+    uint64_t hit[P];                          // columns of the panel a bin column taps
+    __align__(16) float stile[CHK * P * P];
+};
+
+// Column offsets come from an LDS table and not from registers kept over a chunk's rows (the
+// registers cost a wave per SIMD: 70 us against 44 us on the batch above); five waves per
+// SIMD by spilling 12 registers is slower too (50 us).
+template <typename T, typename TO, int P, int CX, int CHK, int CPL, int D>
+__global__ __launch_bounds__(256) void fwd_any_kernel(FwdArgs args) {
+    constexpr int NB = P * P;
+    constexpr int RPW = (P + 3) / 4;          // bin rows per wave
+    constexpr int SLICE = 64 * CPL;
+    static_assert(RPW <= 4 && 64 % kAnyRows == 0 && kAnyCols == 64 && kAnyCols % CX == 0, "tables");
+    __shared__ AnyFwdSmem<P, CHK> sm;
+    (void)args;
+    const FwdArgs &a = *(const FwdArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    const LevelTable &lv = a.lv;
+    const uint32_t lid = xcd_remap(blockIdx.x, gridDim.x);
+    const int slot = static_cast<int>(lid / static_cast<uint32_t>(a.wg_per_roi));
+    const int sub = static_cast<int>(lid) - slot * a.wg_per_roi;
+    const int slice0 = sub * a.spw;
+    const int slice1 = min(a.nslices, slice0 + a.spw);
+    int k = uniform_i(a.perm ? a.perm[slot] : slot);
+    const bool kvalid = k >= 0 && k < a.K;
+    if (!kvalid) k = 0;
+    const float *r = a.rois + 5 * static_cast<int64_t>(k);
+    const float rb = r[0], x1 = r[1], y1 = r[2], x2 = r[3], y2 = r[4];
+    const int lvl = uniform_i(a.roi_levels ? a.roi_levels[k] : 0);
+    const bool lvalid = lvl >= 0 && lvl < lv.num;
+    const LevelArg L = level_at(lv, lvalid ? lvl : 0);
+    const int b = roi_batch(rb, lv.N);
+    Axis ax = axis_setup(x1, x2, L.scale, a.aligned, P, a.S);
+    Axis ay = axis_setup(y1, y2, L.scale, a.aligned, P, a.S);
+    ax.grid = uniform_i(ax.grid);
+    ay.grid = uniform_i(ay.grid);
+    // an adaptive grid may be empty (a box without extent): every output is zero
+    const bool active = kvalid && lvalid && b >= 0 && ax.grid > 0 && ay.grid > 0;
+
+    const int t = threadIdx.x;
+    const int wave = uniform_i(t >> 6);
+    const int lane = t & 63;
+    const int p0 = min(P, wave * RPW);
+    const int p1 = min(P, p0 + RPW);
+    const uint32_t sh_b = static_cast<uint32_t>(L.sh * int64_t(sizeof(T)));
+    const uint32_t sw_b = static_cast<uint32_t>(L.sw * int64_t(sizeof(T)));
+    const float *const ypos = sm.pos;
+    const float *const xpos = sm.pos + kAnyGrid * P;
+
+    if (active) any_positions<P>(ay, ax, L.H, L.W, sm.pos);
+    __syncthreads();
+    // The wave's tapped rows and the RoI's tapped columns (every wave finds them itself).
+    int ya = 0, ny = 0, xa = 0, xb = 0, nx = 0;
+    if (active) {
+        float ylo = 3e38f, yhi = -1.0f, xlo = 3e38f, xhi = -1.0f;
+        for (int u = p0 * ay.grid + lane; u < p1 * ay.grid; u += 64) {
+            const float v = ypos[u];
+            if (v >= 0.0f) {
+                ylo = fminf(ylo, v);
+                yhi = fmaxf(yhi, v);
+            }
+        }
+        for (int u = lane; u < P * ax.grid; u += 64) {
+            const float v = xpos[u];
+            if (v >= 0.0f) {
+                xlo = fminf(xlo, v);
+                xhi = fmaxf(xhi, v);
+            }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            ylo = fminf(ylo, __shfl_xor(ylo, o));
+            yhi = fmaxf(yhi, __shfl_xor(yhi, o));
+            xlo = fminf(xlo, __shfl_xor(xlo, o));
+            xhi = fmaxf(xhi, __shfl_xor(xhi, o));
+        }
+        if (yhi >= 0.0f) {
+            ya = uniform_i(static_cast<int>(ylo));
+            ny = uniform_i(min(static_cast<int>(yhi) + 1, L.H - 1)) - ya + 1;
+        }
+        if (xhi >= 0.0f) {
+            xa = uniform_i(static_cast<int>(xlo));
+            xb = uniform_i(min(static_cast<int>(xhi) + 1, L.W - 1));
+            nx = xb - xa + 1;
+        }
+    }
+    const int npx = (nx + kAnyCols - 1) / kAnyCols;   // the same in every wave
+    const int npy = (ny + kAnyRows - 1) / kAnyRows;   // the wave's own
+    const float inv_count = 1.0f / static_cast<float>(max(ay.grid * ax.grid, 1));
+
+    uint32_t cmask = 0;
+    for (int slice = slice0; slice < slice1; ++slice) {
+        if (slice > slice0) __syncthreads();   // the previous slice's output tile is stored
+        const int c = slice * SLICE + lane * CPL;
+        const bool lane_on = active && c < lv.C;
+        const char *img = static_cast<const char *>(L.data) +
+                          (active ? static_cast<int64_t>(b) * L.sn * int64_t(sizeof(T)) : 0);
+        const __amdgpu_buffer_rsrc_t res = make_rsrc(img, L.img_bytes);
+        const uint32_t vbase = lane_on ? static_cast<uint32_t>(c) * uint32_t(sizeof(T)) : kBufOOB;
+
+        float acc[CPL][RPW][P];
+#pragma unroll
+        for (int j = 0; j < CPL; ++j)
+#pragma unroll
+            for (int p = 0; p < RPW; ++p)
+#pragma unroll
+                for (int q = 0; q < P; ++q) acc[j][p][q] = 0.0f;
+
+        for (int px = 0; px < npx; ++px) {
+            const int X0 = xa + px * kAnyCols;
+            // column weights of the panel: a wave takes whole bin columns, lane = column
+            if (slice == slice0 || npx > 1) {
+                if (px > 0 || slice > slice0) __syncthreads();   // the last panel is consumed
+                // columns past the last tapped one repeat it (their weights are zero)
+                if (wave == 3) sm.xoff[lane] = static_cast<uint32_t>(min(X0 + lane, xb)) * sw_b;
+                for (int q = wave; q < P; q += 4) {
+                    bool h = false;
+                    float w = 0.0f;
+                    if (X0 + lane <= xb)
+                        w = any_weight(xpos + q * ax.grid, ax, q, X0 + lane, L.W, h);
+                    sm.wx[q][lane] = w;
+                    const uint64_t m = __ballot(h);
+                    if (lane == 0) sm.hit[q] = m;
+                }
+                __syncthreads();
+                // bin columns each chunk of CX columns reaches, lane = chunk
+                cmask = 0;
+                if (lane < kAnyCols / CX) {
+#pragma unroll
+                    for (int q = 0; q < P; ++q)
+                        cmask |= ((sm.hit[q] >> (lane * CX)) & ((1u << CX) - 1u)) ? 1u << q : 0u;
+                }
+            }
+            const int nch = (min(kAnyCols, xb - X0 + 1) + CX - 1) / CX;
+            for (int py = 0; py < npy; ++py) {
+                const int Y0 = ya + py * kAnyRows;
+                const int rows = min(kAnyRows, ya + ny - Y0);
+                // row weights of the panel (the wave's own): lanes over (bin row, row)
+                if ((slice == slice0 && px == 0) || npy > 1) {
+                    wave_sync();   // the last panel's are consumed
+#pragma unroll
+                    for (int pp = 0; pp < (RPW * kAnyRows + 63) / 64; ++pp) {
+                        const int u = pp * 64 + lane;
+                        const int p = u / kAnyRows, y = u % kAnyRows;
+                        float w = 0.0f;
+                        bool h = false;
+                        if (p < RPW && p0 + p < p1 && y < rows)
+                            w = any_weight(ypos + (p0 + p) * ay.grid, ay, p0 + p, Y0 + y, L.H, h);
+                        if (p < RPW) sm.wy[wave][y][p] = w;
+                    }
+                    wave_sync();
+                }
+                float H[CPL][CX][RPW];
+#pragma unroll
+                for (int j = 0; j < CPL; ++j)
+#pragma unroll
+                    for (int x = 0; x < CX; ++x)
+#pragma unroll
+                        for (int p = 0; p < RPW; ++p) H[j][x][p] = 0.0f;
+
+                auto issue = [&](int ch, int yi, AnyPix<T, CPL> (&v)[CX]) {
+                    const uint32_t rowb = vbase + static_cast<uint32_t>(Y0 + yi) * sh_b;
+                    const uint32_t *xo = sm.xoff + ch * CX;
+#pragma unroll
+                    for (int x = 0; x < CX; ++x) any_load<T, CPL>(res, rowb + xo[x], 0, v[x]);
+                };
+                auto consume = [&](int ch, int yi, const AnyPix<T, CPL> (&v)[CX]) {
+                    const float *wy = sm.wy[wave][yi];
+#pragma unroll
+                    for (int x = 0; x < CX; ++x)
+#pragma unroll
+                        for (int j = 0; j < CPL; ++j) {
+                            const float f = any_value<T, CPL>(v[x], j);
+#pragma unroll
+                            for (int p = 0; p < RPW; ++p) H[j][x][p] = fmaf(wy[p], f, H[j][x][p]);
+                        }
+                    if (yi == rows - 1) {
+                        // the chunk's columns into the bin columns that tap them
+                        const uint32_t m = __builtin_amdgcn_readlane(cmask, ch);
+#pragma unroll
+                        for (int q = 0; q < P; ++q) {
+                            if (!((m >> q) & 1u)) continue;
+                            float wq[CX];
+#pragma unroll
+                            for (int x4 = 0; x4 < CX; x4 += 4) {
+                                const float4 w4 =
+                                    *reinterpret_cast<const float4 *>(&sm.wx[q][ch * CX + x4]);
+                                wq[x4] = w4.x;
+                                wq[x4 + 1] = w4.y;
+                                wq[x4 + 2] = w4.z;
+                                wq[x4 + 3] = w4.w;
+                            }
+#pragma unroll
+                            for (int x = 0; x < CX; ++x)
+#pragma unroll
+                                for (int j = 0; j < CPL; ++j)
+#pragma unroll
+                                    for (int p = 0; p < RPW; ++p)
+                                        acc[j][p][q] = fmaf(wq[x], H[j][x][p], acc[j][p][q]);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+#pragma unroll
+                        for (int x = 0; x < CX; ++x)
+#pragma unroll
+                            for (int j = 0; j < CPL; ++j)
+#pragma unroll
+                                for (int p = 0; p < RPW; ++p) H[j][x][p] = 0.0f;
+                    }
+                };
+
+                constexpr int NBUF = D + 1;
+                AnyPix<T, CPL> v[NBUF][CX];
+                const int units = rows * nch;
+                int ic = 0, iy = 0, cc = 0, cy = 0;   // next unit to issue, to consume
+                auto issue_next = [&](AnyPix<T, CPL> (&dst)[CX]) {
+                    issue(ic, iy, dst);
+                    if (++iy == rows) {
+                        iy = 0;
+                        ++ic;
+                    }
+                };
+#pragma unroll
+                for (int d = 0; d < D; ++d)
+                    if (d < units) issue_next(v[d]);
+                for (int u0 = 0; u0 < units; u0 += NBUF) {
+#pragma unroll
+                    for (int jj = 0; jj < NBUF; ++jj) {
+                        if (u0 + jj >= units) break;
+                        if (u0 + jj + D < units) issue_next(v[(jj + D) % NBUF]);
+                        __builtin_amdgcn_sched_barrier(0);
+                        consume(cc, cy, v[jj]);
+                        if (++cy == rows) {
+                            cy = 0;
+                            ++cc;
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+        }
+
+        // A zero weight times a non-finite feature may have reached bins whose samples do
+        // not tap it, and shows as a non-finite output of the wave: then its bins are
+        // recomputed sample by sample, every product taken where the definition takes it.
+        uint32_t bad = 0;
+#pragma unroll
+        for (int j = 0; j < CPL; ++j)
+#pragma unroll
+            for (int p = 0; p < RPW; ++p)
+#pragma unroll
+                for (int q = 0; q < P; ++q) {
+                    acc[j][p][q] *= inv_count;
+                    bad |= __builtin_isfinite(acc[j][p][q]) ? 0u : 1u;
+                }
+        if (__builtin_amdgcn_ballot_w64(bad != 0) != 0) {
+#pragma unroll
+            for (int j = 0; j < CPL; ++j) {
+                const uint32_t vb = vbase + static_cast<uint32_t>(j) * uint32_t(sizeof(T));
+#pragma unroll
+                for (int p = 0; p < RPW; ++p) {
+                    if (p0 + p >= p1) continue;
+#pragma unroll 1
+                    for (int q = 0; q < P; ++q) {
+                        float sum = 0.0f;
+                        for (int iy = 0; iy < ay.grid; ++iy) {
+                            const float vy = ypos[(p0 + p) * ay.grid + iy];
+                            if (vy < 0.0f) continue;
+                            const int yl = static_cast<int>(vy);
+                            const float fy = vy - static_cast<float>(yl);
+                            const uint32_t r0 = vb + static_cast<uint32_t>(yl) * sh_b;
+                            const uint32_t r1 = vb + static_cast<uint32_t>(min(yl + 1, L.H - 1)) * sh_b;
+                            for (int ix = 0; ix < ax.grid; ++ix) {
+                                const float vx = xpos[q * ax.grid + ix];
+                                if (vx < 0.0f) continue;
+                                const int xl = static_cast<int>(vx);
+                                const float fx = vx - static_cast<float>(xl);
+                                const uint32_t cl = static_cast<uint32_t>(xl) * sw_b;
+                                const uint32_t chh = static_cast<uint32_t>(min(xl + 1, L.W - 1)) * sw_b;
+                                const float v00 = raw_to_f32<T>(buf_load_raw<T>(res, r0 + cl));
+                                const float v01 = raw_to_f32<T>(buf_load_raw<T>(res, r0 + chh));
+                                const float v10 = raw_to_f32<T>(buf_load_raw<T>(res, r1 + cl));
+                                const float v11 = raw_to_f32<T>(buf_load_raw<T>(res, r1 + chh));
+                                const float xl_ = fmaf(fx, v01, (1.0f - fx) * v00);
+                                const float xh_ = fmaf(fx, v11, (1.0f - fx) * v10);
+                                sum += fmaf(fy, xh_, (1.0f - fy) * xl_);
+                            }
+                        }
+                        sum = sum / static_cast<float>(max(ay.grid * ax.grid, 1));
+#pragma unroll
+                        for (int qq = 0; qq < P; ++qq) acc[j][p][qq] = (qq == q) ? sum : acc[j][p][qq];
+                    }
+                }
+            }
+        }
+
+        // the slice's [SLICE][P][P] block, transposed through LDS in rounds of CHK channels
+        const int nchan = min(SLICE, lv.C - slice * SLICE);
+        const gptr<TO> out_blk = as_global_mut<TO>(a.out) +
+                                 (static_cast<int64_t>(k) * lv.C + static_cast<int64_t>(slice) * SLICE) * NB;
+#pragma unroll
+        for (int c0 = 0; c0 < SLICE; c0 += CHK) {
+            if (lane * CPL >= c0 && lane * CPL < c0 + CHK) {
+#pragma unroll
+                for (int j = 0; j < CPL; ++j)
+#pragma unroll
+                    for (int p = 0; p < RPW; ++p) {
+                        if (p0 + p >= p1) continue;
+#pragma unroll
+                        for (int q = 0; q < P; ++q)
+                            sm.stile[(lane * CPL + j - c0) * NB + (p0 + p) * P + q] = acc[j][p][q];
+                    }
+            }
+            __syncthreads();
+            const int ne = max(0, min(CHK, nchan - c0)) * NB;
+            if (kvalid) store_run_f32<TO>(out_blk + c0 * NB, sm.stile, ne, t, 256);
+            if (c0 + CHK < SLICE) __syncthreads();
+        }
+    }
+}
+
+template <typename T, typename TO, int P, int CX, int CHK, int CPL, int D>
+static hipError_t launch_any(FwdArgs a, hipStream_t stream) {
+    a.nslices = (a.lv.C + 64 * CPL - 1) / (64 * CPL);
+    // slices per workgroup as in the two-samples forward: up to 4 share the geometry while
+    // the grid keeps at least 32 workgroups per CU
+    a.spw = 1;
+    for (int spw = 4; spw > 1; spw /= 2)
+        if (static_cast<int64_t>(a.K) * ((a.nslices + spw - 1) / spw) >= 8192) {
+            a.spw = spw;
+            break;
+        }
+    a.wg_per_roi = (a.nslices + a.spw - 1) / a.spw;
+    const int64_t grid = static_cast<int64_t>(a.K) * a.wg_per_roi;
+    if (grid >= (int64_t(1) << 24)) return hipErrorInvalidConfiguration;
+    fwd_any_kernel<T, TO, P, CX, CHK, CPL, D><<<static_cast<uint32_t>(grid), 256, 0, stream>>>(a);
+    return hipGetLastError();
+}
+
+template <typename T, typename TO>
+hipError_t launch_fwd_any_typed(const FwdArgs &a, hipStream_t stream) {
+    // columns per unit, channels per lane and units in flight of the two-samples kernels
+    if (a.PH == 7) {
+        if constexpr (sizeof(T) == 2)
+            if (a.lv.C % 2 == 0) return launch_any<T, TO, 7, 4, 64, 2, 4>(a, stream);
+        return launch_any<T, TO, 7, 8, 64, 1, 2>(a, stream);
+    }
+    return launch_any<T, TO, 14, 4, 16, 1, 2>(a, stream);
+}
+
+hipError_t launch_fwd_any(const FwdArgs &a, int feat_dtype, int out_dtype, hipStream_t stream) {
+    if (feat_dtype == kF32)
+        return out_dtype == kF32 ? launch_fwd_any_typed<float, float>(a, stream)
+                                 : launch_fwd_any_typed<float, uint16_t>(a, stream);
+    return out_dtype == kF32 ? launch_fwd_any_typed<uint16_t, float>(a, stream)
+                             : launch_fwd_any_typed<uint16_t, uint16_t>(a, stream);
+}
+
+// ---------------------------------------------------------------------------
+// Backward: tile gather
+// ---------------------------------------------------------------------------
+//
+// The two-samples gather (bwd.hip) with the weights of a quadrant summed from the RoI's
+// sample positions, which the workgroup puts in LDS while the RoI's gradient block is
+// copied.  The tile lists hold every RoI whose samples can tap the tile, whatever their
+// number.  A non-finite sum in a tile (a NaN or infinity upstream, or an overflow) makes
+// the workgroup walk its list once more, adding every product only where a sample taps
+// the pixel, as the scatter does.
+template <typename TG, int P>
+struct AnyGatherSmem {
+    static constexpr int T = 8;
+    static constexpr int NB = P * P;
+    static constexpr int GB = 64 * NB;
+    static constexpr int RUN = sizeof(TG) == 4 ? 256 : 64;
+    static constexpr int NRUN = (GB + RUN - 1) / RUN;
+    static constexpr int GBP = NRUN * RUN;
+    static constexpr int NBUF = 2 * GBP * 4 <= 53248 ? 2 : 1;
+    float pos[NBUF][2 * P * kAnyGrid];
+    __align__(16) float wy[4][P * T];
+    __align__(16) float wx[4][P * T];
+    int k[64];
+    Axis ax[64], ay[64];
+    int rng[64][4];   // tap extent ymin, ymax, xmin, xmax
+    int n;
+};
+
+// One bin's products added to the gradient in memory where its samples tap the pixel: bit r
+// of rb (q of qb) marks a tapped row (column) of the quadrant at byte `base` of the image.
+// The workgroup owns the tile and the lane its channel, so plain adds do.
+__device__ __forceinline__ void gather_exact_bin(__amdgpu_buffer_rsrc_t dst, uint32_t vo,
+                                                 uint32_t base, uint32_t sh4, uint32_t sw4, float g,
+                                                 const float *wy, const float *wx, uint32_t rb,
+                                                 uint32_t qb) {
+#pragma unroll 1
+    for (uint32_t rm = rb; rm; rm &= rm - 1) {
+        const int r = __builtin_ctz(rm);
+        const float gy = wy[r] * g;
+#pragma unroll 1
+        for (uint32_t qm = qb; qm; qm &= qm - 1) {
+            const int q = __builtin_ctz(qm);
+            const uint32_t o = base + static_cast<uint32_t>(r) * sh4 + static_cast<uint32_t>(q) * sw4;
+            const float old = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dst, vo, o, 0));
+            const float v = fmaf(wx[q], gy, old);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), dst, vo, o, 0);
+            __builtin_amdgcn_s_waitcnt(0x0F70);   // before the next bin reads the pixel
+        }
+    }
+}
+
+// Walks the tile's RoIs; add(gl, wy, wx, yb, xb, pha, phb, pwa, pwb) takes one RoI's part of
+// the wave's quadrant: the lane's gradient block gl, the weights (wy with 1 / count), the
+// tapped (bin, pixel) pairs as ballots, and the runs of bins that reach the quadrant.
+template <typename TG, int P, typename Add>
+__device__ __forceinline__ void any_phase(const GatherHead &h, const LevelTable &lv, int S, int t,
+                                          const GatherTile &x, AnyGatherSmem<TG, P> &sm,
+                                          uint32_t *slot0, uint32_t *slot1, Add &&add) {
+    using SM = AnyGatherSmem<TG, P>;
+    constexpr int T = SM::T, NB = SM::NB, GB = SM::GB, NBUF = SM::NBUF;
+    constexpr int NP = (P * T + 63) / 64;   // ballot passes for the weights of an axis
+    const int tid = threadIdx.x;
+    const int wave = uniform_i(tid >> 6);
+    const int lane = tid & 63;
+    const LevelArg &L = x.L;
+    const int l = x.l, b = x.b, R0 = x.R0, Q0 = x.Q0;
+    int s0 = h.tile_start[t];
+    int s1 = h.tile_end[t];
+    s0 = max(0, min(s0, h.capacity));
+    s1 = max(s0, min(s1, h.capacity));
+    float *wy = sm.wy[wave];
+    float *wx = sm.wx[wave];
+    const int64_t kstride = static_cast<int64_t>(lv.C) * NB;
+    const int nvalid = x.nch * NB;
+    const bool wide = sizeof(TG) == 4 && (lv.C & 3) == 0 &&
+                      (reinterpret_cast<uintptr_t>(h.gout) & 15u) == 0;
+    // copy of kept RoI j's gradient block into LDS (as in bwd.hip's gather)
+    auto fetch = [&](int j, uint32_t *gdst) {
+        const int k = uniform_i(sm.k[j]);
+        const char *src = static_cast<const char *>(h.gout) +
+                          (static_cast<int64_t>(x.cg) * 64 * NB + static_cast<int64_t>(k) * kstride) *
+                              int64_t(sizeof(TG));
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(src, static_cast<uint32_t>(nvalid) * uint32_t(sizeof(TG)));
+        constexpr int RUN = SM::RUN, NRUN = SM::NRUN;
+        if (RUN == 256 && wide) {
+#pragma unroll
+            for (int m = 0; m < (NRUN + 3) / 4; ++m) {
+                const int run = wave + 4 * m;
+                if (m < NRUN / 4 || run < NRUN) {
+                    auto *dst = (__attribute__((address_space(3))) void *)(gdst + RUN * run);
+                    const uint32_t off = static_cast<uint32_t>(RUN * run + lane * 4) * 4u;
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, off, 0, 0, 0);
+                }
+            }
+        } else {
+            constexpr int NR64 = GB / 64;
+#pragma unroll
+            for (int m = 0; m < (NR64 + 3) / 4; ++m) {
+                const int run = wave + 4 * m;
+                if (m < NR64 / 4 || run < NR64) {
+                    auto *dst = (__attribute__((address_space(3))) void *)(gdst + 64 * run);
+                    const uint32_t off = static_cast<uint32_t>(64 * run + lane) * uint32_t(sizeof(TG));
+                    if constexpr (sizeof(TG) == 4)
+                        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 4, off, 0, 0, 0);
+                    else
+                        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 2, off, 0, 0, 0);
+                }
+            }
+        }
+    };
+    auto fetch_wait = [&]() { __builtin_amdgcn_s_waitcnt(0x0F70); };
+    auto positions = [&](int j, float *pos) { any_positions<P>(sm.ay[j], sm.ax[j], L.H, L.W, pos); };
+    auto consume = [&](int j, const uint32_t *gsrc, const float *pos) {
+        const int ymin = sm.rng[j][0], ymax = sm.rng[j][1];
+        const int xmin = sm.rng[j][2], xmax = sm.rng[j][3];
+        if (!x.wave_on || ymax < R0 || ymin >= R0 + T || xmax < Q0 || xmin >= Q0 + T) return;
+        const Axis ay = sm.ay[j], ax = sm.ax[j];
+        const float inv_count = 1.0f / static_cast<float>(max(ay.grid * ax.grid, 1));
+        uint64_t yb[NP], xb[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int u = p * 64 + lane;
+            bool hy = false, hx = false;
+            if (u < P * T) {
+                const int bin = u / T;
+                const float w = any_weight(pos + bin * ay.grid, ay, bin, R0 + (u % T), L.H, hy);
+                wy[u] = w * inv_count;
+                wx[u] = any_weight(pos + kAnyGrid * P + bin * ax.grid, ax, bin, Q0 + (u % T), L.W, hx);
+            }
+            yb[p] = __ballot(hy);
+            xb[p] = __ballot(hx);
+        }
+        const int pha = first_set(yb) / T, phb = last_set(yb) / T;
+        const int pwa = first_set(xb) / T, pwb = last_set(xb) / T;
+        if (first_set(yb) < 0 || first_set(xb) < 0) return;
+        wave_sync();
+        add(gsrc + lane * NB, wy, wx, yb, xb, pha, phb, pwa, pwb);
+    };
+
+    for (int base = s0; base < s1; base += 64) {
+        const int n = min(64, s1 - base);
+        __syncthreads();   // previous batch fully consumed
+        if (wave == 0) {
+            bool keep = false;
+            int k = 0, ymin = 0, ymax = -1, xmin = 0, xmax = -1;
+            Axis ax{}, ay{};
+            if (lane < n) {
+                k = h.tile_rois[base + lane];
+                if (k >= 0 && k < h.K) {
+                    const float *r = h.rois + 5 * static_cast<int64_t>(k);
+                    const float r0 = r[0], x1 = r[1], y1 = r[2], x2 = r[3], y2 = r[4];
+                    const int lvl = h.roi_levels ? h.roi_levels[k] : 0;
+                    if (lvl == l && roi_batch(r0, lv.N) == b) {
+                        ax = axis_setup(x1, x2, L.scale, h.aligned, P, S);
+                        ay = axis_setup(y1, y2, L.scale, h.aligned, P, S);
+                        if (ax.grid > 0 && ay.grid > 0) {
+                            // extent from the end samples (either may come first in an
+                            // inverted box); an end sample off the map widens it to the edge
+                            const Tap fy = axis_tap(ay, 0, 0, L.H);
+                            const Tap ly = axis_tap(ay, P - 1, ay.grid - 1, L.H);
+                            const Tap fx = axis_tap(ax, 0, 0, L.W);
+                            const Tap lx = axis_tap(ax, P - 1, ax.grid - 1, L.W);
+                            const bool yok = fy.lo >= 0 && ly.lo >= 0;
+                            const bool xok = fx.lo >= 0 && lx.lo >= 0;
+                            const bool ydn = !(ay.bin >= 0.0f), xdn = !(ax.bin >= 0.0f);
+                            ymin = yok ? min(fy.lo, ly.lo) : ydn || fy.lo < 0 ? 0 : fy.lo;
+                            ymax = yok ? max(fy.hi, ly.hi) : ydn || ly.lo < 0 ? L.H - 1 : ly.hi;
+                            xmin = xok ? min(fx.lo, lx.lo) : xdn || fx.lo < 0 ? 0 : fx.lo;
+                            xmax = xok ? max(fx.hi, lx.hi) : xdn || lx.lo < 0 ? L.W - 1 : lx.hi;
+                            keep = ymax >= x.WR0 && ymin < x.WR1 && xmax >= x.WC0 && xmin < x.WC1;
+                        }
+                    }
+                }
+            }
+            const uint64_t km = __ballot(keep);
+            if (keep) {
+                const int pos = static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+                    static_cast<uint32_t>(km >> 32),
+                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(km), 0u)));
+                sm.k[pos] = k;
+                sm.ax[pos] = ax;
+                sm.ay[pos] = ay;
+                sm.rng[pos][0] = ymin;
+                sm.rng[pos][1] = ymax;
+                sm.rng[pos][2] = xmin;
+                sm.rng[pos][3] = xmax;
+            }
+            if (lane == 0) sm.n = __builtin_popcountll(km);
+        }
+        __syncthreads();
+        const int nk = uniform_i(sm.n);
+        if (nk == 0) continue;
+        if constexpr (NBUF == 2) {
+            fetch(0, slot0);
+            positions(0, sm.pos[0]);
+            fetch_wait();
+            __syncthreads();
+            for (int j = 0; j < nk; j += 2) {
+                if (j + 1 < nk) {
+                    fetch(j + 1, slot1);
+                    positions(j + 1, sm.pos[1]);
+                }
+                consume(j, slot0, sm.pos[0]);
+                fetch_wait();
+                __syncthreads();
+                if (j + 1 >= nk) break;
+                if (j + 2 < nk) {
+                    fetch(j + 2, slot0);
+                    positions(j + 2, sm.pos[0]);
+                }
+                consume(j + 1, slot1, sm.pos[1]);
+                fetch_wait();
+                __syncthreads();
+            }
+        } else {
+            for (int j = 0; j < nk; ++j) {
+                if (j > 0) __syncthreads();   // the previous block is fully consumed
+                fetch(j, slot0);
+                positions(j, sm.pos[0]);
+                fetch_wait();
+                __syncthreads();
+                consume(j, slot0, sm.pos[0]);
+            }
+        }
+    }
+}
+
+// 7x7: held to 128 registers (137 without, three waves per SIMD: 70 us against 58 us on the
+// batch above); 14x14: its 50 KiB block allows two workgroups per CU anyway.
+template <typename TG, int P>
+__global__ __launch_bounds__(256, P == 7 ? 4 : 2) void bwd_gather_any_kernel(GatherArgs a) {
+    using SM = AnyGatherSmem<TG, P>;
+    constexpr bool two = SM::NBUF == 2;
+    __shared__ SM sm;
+    __shared__ __align__(16) uint32_t blk0[SM::GBP];
+    __shared__ __align__(16) uint32_t blk1[two ? SM::GBP : 1];
+    GatherTile x;
+    const int t = gather_tile(a, a.tile_order, x);
+    constexpr int NP = (P * 8 + 63) / 64;
+    uint32_t *const slot1 = two ? blk1 : nullptr;
+    float acc[8][8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc[r][q] = 0.0f;
+    any_phase<TG, P>(a.head[0], a.lv, a.S, t, x, sm, blk0, slot1,
+                     [&](const uint32_t *gl, const float *wy, const float *wx, const uint64_t (&yb)[NP],
+                         const uint64_t (&)[NP], int pha, int phb, int pwa, int pwb) {
+                         gather_rows<TG, P>(acc, gl + pwa, wx + pwa * 8, wy, yb, pha, phb,
+                                            pwb - pwa + 1);
+                     });
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) bad = bad || !__builtin_isfinite(acc[r][q]);
+    static_assert(SM::GBP >= 4 * 512, "store scratch in the first slot");
+    // also the barrier after which the staging slots are free
+    if (!__syncthreads_or(bad && x.wave_on)) {
+        gather_store(x, a.zero_init, acc, reinterpret_cast<float *>(blk0) + (threadIdx.x >> 6) * 512);
+        return;
+    }
+    // The exact walk: the quadrant cleared in memory, then every product added there (the
+    // accumulators are free, so this rare path costs the other no registers).
+    const int lane = threadIdx.x & 63;
+    const char *img = static_cast<const char *>(x.L.data) + static_cast<int64_t>(x.b) * x.L.sn * 4;
+    const __amdgpu_buffer_rsrc_t dst = make_rsrc(img, x.L.img_bytes);
+    const uint32_t vo = lane < x.nch ? static_cast<uint32_t>(x.cg * 64 + lane) *
+                                           static_cast<uint32_t>(x.L.sc) * 4u
+                                     : kBufOOB;
+    const uint32_t sh4 = static_cast<uint32_t>(x.L.sh) * 4u, sw4 = static_cast<uint32_t>(x.L.sw) * 4u;
+    const uint32_t base = static_cast<uint32_t>(x.R0) * sh4 + static_cast<uint32_t>(x.Q0) * sw4;
+    if (a.zero_init && x.wave_on) {
+        const int nr = min(8, x.L.H - x.R0), nq = min(8, x.L.W - x.Q0);
+#pragma unroll 1
+        for (int r = 0; r < nr; ++r)
+#pragma unroll 1
+            for (int q = 0; q < nq; ++q)
+                __builtin_amdgcn_raw_buffer_store_b32(0u, dst, vo, base + static_cast<uint32_t>(r) * sh4 +
+                                                      static_cast<uint32_t>(q) * sw4, 0);
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+    }
+    any_phase<TG, P>(a.head[0], a.lv, a.S, t, x, sm, blk0, slot1,
+                     [&](const uint32_t *gl, const float *wy, const float *wx, const uint64_t (&yb)[NP],
+                         const uint64_t (&xb)[NP], int pha, int phb, int pwa, int pwb) {
+#pragma unroll 1
+                         for (int ph = pha; ph <= phb; ++ph) {
+                             const uint32_t rb =
+                                 static_cast<uint32_t>(yb[NP == 1 ? 0 : ph >> 3] >> ((ph & 7) * 8)) & 0xffu;
+#pragma unroll 1
+                             for (int pw = pwa; pw <= pwb; ++pw) {
+                                 const uint32_t qb = static_cast<uint32_t>(
+                                     xb[NP == 1 ? 0 : pw >> 3] >> ((pw & 7) * 8)) & 0xffu;
+                                 gather_exact_bin(dst, vo, base, sh4, sw4, raw_to_f32<TG>(gl[ph * P + pw]),
+                                                  wy + ph * 8, wx + pw * 8, rb, qb);
+                             }
+                         }
+                     });
+}
+
+// The RoIs whose level differs from the one the plan gave them (a caller may pass levels of
+// its own): no tile list of their level holds them, so they are scattered with atomics.
+// Plan slot s belongs to the level whose slot range holds it.
+template <typename TG>
+__global__ __launch_bounds__(256) void bwd_stray_kernel(GatherArgs a) {
+    const GatherHead &h = a.head[0];
+    const int s = static_cast<int>(blockIdx.x) * 256 + static_cast<int>(threadIdx.x);
+    const int lane = threadIdx.x & 63;
+    int k = -1, lvl = -1;
+    if (s < h.K) {
+        k = h.perm[s];
+        if (k >= 0 && k < h.K) {
+            int planned = 0;
+            for (int i = 1; i < a.lv.num; ++i) planned += s >= h.offsets[i] ? 1 : 0;
+            lvl = h.roi_levels ? h.roi_levels[k] : 0;
+            if (lvl == planned || lvl < 0 || lvl >= a.lv.num) k = -1;
+        } else {
+            k = -1;
+        }
+    }
+    uint64_t todo = __ballot(k >= 0);
+    while (todo) {
+        const int src = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const int kk = __shfl(k, src);
+        const int ll = __shfl(lvl, src);
+        const float *r = h.rois + 5 * static_cast<int64_t>(kk);
+        const int b = roi_batch(r[0], a.lv.N);
+        if (b < 0) continue;
+        const LevelArg L = level_at(a.lv, uniform_i(ll));
+        const Axis ax = axis_setup(r[1], r[3], L.scale, h.aligned, a.PW, a.S);
+        const Axis ay = axis_setup(r[2], r[4], L.scale, h.aligned, a.PH, a.S);
+        const int nb = a.PH * a.PW;
+        const int64_t n = static_cast<int64_t>(a.lv.C) * nb;
+        for (int64_t e = lane; e < n; e += 64) {
+            const int64_t c = e / nb;
+            const int j = static_cast<int>(e - c * nb);
+            const int ph = j / a.PW, pw = j - (j / a.PW) * a.PW;
+            const float g = load_f32(as_global<TG>(h.gout) + kk * n + e) /
+                            static_cast<float>(max(ay.grid * ax.grid, 1));
+            float *base = static_cast<float *>(const_cast<void *>(L.data)) + b * L.sn + c * L.sc;
+            for (int iy = 0; iy < ay.grid; ++iy) {
+                const Tap ty = axis_tap(ay, ph, iy, L.H);
+                if (ty.lo < 0) continue;
+                for (int ix = 0; ix < ax.grid; ++ix) {
+                    const Tap tx = axis_tap(ax, pw, ix, L.W);
+                    if (tx.lo < 0) continue;
+                    unsafeAtomicAdd(base + ty.lo * L.sh + tx.lo * L.sw, g * (ty.wlo * tx.wlo));
+                    unsafeAtomicAdd(base + ty.lo * L.sh + tx.hi * L.sw, g * (ty.wlo * tx.whi));
+                    unsafeAtomicAdd(base + ty.hi * L.sh + tx.lo * L.sw, g * (ty.whi * tx.wlo));
+                    unsafeAtomicAdd(base + ty.hi * L.sh + tx.hi * L.sw, g * (ty.whi * tx.whi));
+                }
+            }
+        }
+    }
+}
+
+// `a` prepared (gather_prepare), `grid` its workgroups.
+hipError_t launch_gather_any(const GatherArgs &a, uint32_t grid, int gout_dtype, hipStream_t stream) {
+    const uint32_t g2 = static_cast<uint32_t>((a.head[0].K + 255) / 256);
+    if (gout_dtype == kF32) {
+        if (a.PH == 7) bwd_gather_any_kernel<float, 7><<<grid, 256, 0, stream>>>(a);
+        else bwd_gather_any_kernel<float, 14><<<grid, 256, 0, stream>>>(a);
+        bwd_stray_kernel<float><<<g2, 256, 0, stream>>>(a);
+    } else {
+        if (a.PH == 7) bwd_gather_any_kernel<uint16_t, 7><<<grid, 256, 0, stream>>>(a);
+        else bwd_gather_any_kernel<uint16_t, 14><<<grid, 256, 0, stream>>>(a);
+        bwd_stray_kernel<uint16_t><<<g2, 256, 0, stream>>>(a);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace rex

@@ -430,7 +430,7 @@ re_status_t roi_align_fwd(const re_level_t *levels, int32_t num_levels, const fl
     a.PW = out_w;
     a.S = sampling_ratio;
     a.aligned = aligned;
-    const bool fast = cl && fwd_fast_available(out_h, out_w, sampling_ratio);
+    const bool fast = cl && fixed_grid(out_h, out_w);
     return from_hip(launch_fwd(a, levels[0].dtype, out_dtype, fast,
                                static_cast<hipStream_t>(stream)));
 }
@@ -513,7 +513,7 @@ re_status_t roi_align_fwd_noalloc(const re_level_t *levels, int32_t num_levels, 
     a.PW = out_w;
     a.S = sampling_ratio;
     a.aligned = aligned;
-    const bool fast = cl && fwd_fast_available(out_h, out_w, sampling_ratio);
+    const bool fast = cl && fixed_grid(out_h, out_w);
     return from_hip(launch_fwd(a, levels[0].dtype, out_dtype, fast, s));
 }
 
@@ -573,7 +573,7 @@ re_status_t roi_align_fwd_multi(const re_level_t *levels, int32_t num_levels,
         a.PW = h.out_w;
         a.S = h.sampling_ratio;
         a.aligned = h.aligned;
-        const bool fast = cl && fwd_fast_available(h.out_h, h.out_w, h.sampling_ratio);
+        const bool fast = cl && fixed_grid(h.out_h, h.out_w);
         if ((st = from_hip(launch_fwd(a, levels[0].dtype, out_dtype, fast, s))) != RE_OK) return st;
     }
     if (m.nheads == 0) return RE_OK;
@@ -633,6 +633,36 @@ bool head_gather_ok(const BwdHead &h, const LevelTable &t, const TileLayout &tl)
            gather_available(h.out_h, h.out_w, h.S);
 }
 
+// No two elements of a level share an address (strides grow past the extent of the smaller
+// ones): only then is writing every element once the same as adding to it.
+bool levels_distinct(const LevelTable &t) {
+    for (int l = 0; l < t.num; ++l) {
+        const int64_t ext[4] = {t.N, t.C, t.l[l].H, t.l[l].W};
+        const int64_t str[4] = {t.l[l].sn, t.l[l].sc, t.l[l].sh, t.l[l].sw};
+        bool used[4] = {ext[0] == 1, ext[1] == 1, ext[2] == 1, ext[3] == 1};
+        double span = 1.0;   // elements covered by the dimensions taken so far
+        for (;;) {
+            int d = -1;
+            for (int i = 0; i < 4; ++i)
+                if (!used[i] && (d < 0 || str[i] < str[d])) d = i;
+            if (d < 0) break;
+            if (static_cast<double>(str[d]) < span) return false;
+            span += static_cast<double>(ext[d] - 1) * static_cast<double>(str[d]);
+            used[d] = true;
+        }
+    }
+    return true;
+}
+
+// The tile gather for sampling ratios other than 2 (RE_BWD_AUTO only): a fixed grid, a plan
+// with tile lists, levels the gather can address, and a grid of one dispatch.
+bool head_gather_any_ok(const BwdHead &h, const LevelTable &t, const TileLayout &tl) {
+    if (!h.plan || h.S == 2 || h.K == 0 || tl.ntiles <= 0 || !fixed_grid(h.out_h, h.out_w)) return false;
+    if (!levels_buffered(t) || !levels_distinct(t)) return false;
+    const double side = static_cast<double>(int64_t(1) << (tl.shift - 3));
+    return tl.ntiles * (side * side / 4) * ((t.C + 63) / 64) < double(1 << 24);
+}
+
 GatherHead gather_head(const BwdHead &h, const TileLayout &tl) {
     GatherHead g{};
     const char *ws = static_cast<const char *>(h.plan);
@@ -647,6 +677,8 @@ GatherHead gather_head(const BwdHead &h, const TileLayout &tl) {
     g.capacity = static_cast<int32_t>(tl.capacity);
     g.PH = h.out_h;
     g.PW = h.out_w;
+    g.perm = reinterpret_cast<const int32_t *>(ws + perm_offset());
+    g.offsets = reinterpret_cast<const int32_t *>(ws);
     return g;
 }
 
@@ -681,7 +713,8 @@ re_status_t bwd_head(const BwdHead &h, const LevelTable &t, bool cl, const int64
     const TileLayout tl = tile_layout(t, h.K);
     const bool gather_ok = head_gather_ok(h, t, tl);
     if (algorithm == RE_BWD_GATHER && !gather_ok && h.K > 0) return RE_ERR_UNSUPPORTED;
-    if (gather_ok && algorithm != RE_BWD_SCATTER)
+    if ((gather_ok && algorithm != RE_BWD_SCATTER) ||
+        (algorithm == RE_BWD_AUTO && head_gather_any_ok(h, t, tl)))
         return from_hip(launch_gather(gather_args(t, h, tl, zero_init), h.gdt, s));
     re_status_t st;
     if (zero_init) {

@@ -634,6 +634,8 @@ template <typename T, typename TO>
 static hipError_t launch_fwd_typed(FwdArgs a, bool fast, hipStream_t stream) {
     // a dispatch holds fewer than 2^32 work-items; beyond that, the strided kernel
     if (fast && static_cast<int64_t>(a.K) * ((a.lv.C + 63) / 64) >= (int64_t(1) << 24)) fast = false;
+    if (fast && a.S != 2)
+        return launch_fwd_any(a, sizeof(T) == 2 ? kBF16 : kF32, sizeof(TO) == 2 ? kBF16 : kF32, stream);
     if (fast) {
         if (a.PH == 7) {
             // bf16 features: two adjacent channels per lane (one 32-bit load per pixel)

@@ -178,6 +178,78 @@ __device__ __forceinline__ void gather_store(const GatherTile &x, int zero_init,
     }
 }
 
+// First / last set bit of a multi-word ballot, -1 if none (uniform scalar values).
+template <int P>
+__device__ __forceinline__ int first_set(const uint64_t (&b)[P]) {
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+        if (b[p]) return p * 64 + __builtin_ctzll(b[p]);
+    return -1;
+}
+template <int P>
+__device__ __forceinline__ int last_set(const uint64_t (&b)[P]) {
+#pragma unroll
+    for (int p = P - 1; p >= 0; --p)
+        if (b[p]) return p * 64 + 63 - __builtin_clzll(b[p]);
+    return -1;
+}
+
+// acc[r][q] += yrow[r] * X[q] for the rows r0 .. r0 + NR - 1 of the quadrant.
+template <int R0, int NR>
+__device__ __forceinline__ void outer_rows(float (&acc)[8][8], const float *yrow,
+                                           const float (&X)[8]) {
+    static_assert(R0 % 4 == 0 && NR % 4 == 0, "rows in aligned groups of 4");
+    float yr[8];
+#pragma unroll
+    for (int h = R0 / 4; h < (R0 + NR) / 4; ++h) {
+        const float4 y = *reinterpret_cast<const float4 *>(yrow + 4 * h);
+        yr[4 * h] = y.x;
+        yr[4 * h + 1] = y.y;
+        yr[4 * h + 2] = y.z;
+        yr[4 * h + 3] = y.w;
+    }
+#pragma unroll
+    for (int rr = R0; rr < R0 + NR; ++rr)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc[rr][q] = fmaf(yr[rr], X[q], acc[rr][q]);
+}
+
+// One RoI's contribution to a wave's 8x8 quadrant, for the bin rows pha..phb that
+// reach the quadrant's rows and the npw bin columns pwa.. that reach its columns:
+//   X[q] = sum over pw of Wx[pw][q] * g[ph][pw]
+//   acc[r][q] += Wy[ph][r] * X[q]
+// gl points at g[0][pwa] of this lane's channel, wxa at Wx[pwa][0], wy at Wy[0][0];
+// yb holds the nonzero pattern of Wy (bit ph * 8 + r), which decides the half
+// quadrants (rows 0-3, 4-7) a bin row updates.
+template <typename TG, int PW, int YP>
+__device__ __forceinline__ void gather_rows(float (&acc)[8][8], const uint32_t *gl,
+                                            const float *wxa, const float *wy,
+                                            const uint64_t (&yb)[YP], int pha, int phb, int npw) {
+    for (int ph = pha; ph <= phb; ++ph) {
+        const uint32_t rb = static_cast<uint32_t>(yb[YP == 1 ? 0 : ph >> 3] >> ((ph & 7) * 8)) & 0xffu;
+        if (rb == 0) continue;
+        const uint32_t *gr = gl + ph * PW;
+        // The run of bins is unrolled up to its longest possible length, so every
+        // LDS address is a fixed offset from gr / wxa (no loop-carried pointers, which
+        // would hide from the compiler that these reads do not touch the slot being
+        // filled by the copy in flight).
+        float X[8];
+#pragma unroll
+        for (int i = 0; i < PW; ++i) {
+            if (i >= npw) break;
+            const float gv = raw_to_f32<TG>(gr[i]);
+            const float4 w0 = *reinterpret_cast<const float4 *>(wxa + i * 8);
+            const float4 w1 = *reinterpret_cast<const float4 *>(wxa + i * 8 + 4);
+            const float w[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+#pragma unroll
+            for (int q = 0; q < 8; ++q) X[q] = i == 0 ? w[q] * gv : fmaf(w[q], gv, X[q]);
+        }
+        // rows 0-3 and 4-7 of the quadrant are updated only if the bin row reaches them
+        if (rb & 0x0fu) outer_rows<0, 4>(acc, wy + ph * 8, X);
+        if (rb & 0xf0u) outer_rows<4, 4>(acc, wy + ph * 8, X);
+    }
+}
+
 // Launch-time fields of a gather (block-id decoding without integer division); false
 // when the tile geometry is not one the decoding covers.
 inline bool gather_prepare(GatherArgs &a) {

@@ -83,6 +83,8 @@ struct GatherHead {
     int32_t capacity;
     int32_t PH, PW;
     int32_t pad;
+    const int32_t *perm;         // the plan's order and per-level first slots (bwd_stray_kernel)
+    const int32_t *offsets;
 };
 
 // Division by a divisor fixed at launch, for the block-id decoding of the gather
@@ -385,17 +387,26 @@ hipError_t launch_level_map(const float *rois, int32_t K, int32_t L, float fines
 hipError_t launch_plan(const PlanArgs &a, hipStream_t stream);
 void plan_bands(PlanArgs &a);   // fills nbands, ndiff, band_base, band_rows, dbase
 
-// Forward: `fast` selects the channels-last kernels (every level stride_c == 1 and
-// (PH, PW, S) in the specialised set); otherwise the general strided kernel.
+// The output grids of the specialised RoIAlign kernels.
+inline bool fixed_grid(int PH, int PW) { return PH == PW && (PH == 7 || PH == 14); }
+
+// Forward: `fast` selects the channels-last kernels (every level stride_c == 1 and a
+// fixed_grid; two samples per axis or, in adaptive.hip, any number); otherwise the NCHW or
+// the general strided kernel.  fwd_fast_available: the two-samples kernels' set.
 bool fwd_fast_available(int PH, int PW, int S);
 hipError_t launch_fwd(FwdArgs a, int feat_dtype, int out_dtype, bool fast, hipStream_t stream);
+
+hipError_t launch_fwd_any(const FwdArgs &a, int feat_dtype, int out_dtype, hipStream_t stream);
 
 bool bwd_fast_available(int PH, int PW, int S);
 hipError_t launch_bwd(BwdArgs a, int gout_dtype, bool fast, hipStream_t stream);
 
-// Tile-gather backward (channels-last levels, specialised grids, a plan with tiles).
+// Tile-gather backward (specialised grids, a plan with tiles).  gather_available: the
+// two-samples kernels' set; launch_gather also takes any other sampling ratio on a
+// fixed_grid, one head (launch_gather_any, adaptive.hip).
 bool gather_available(int PH, int PW, int S);
 hipError_t launch_gather(GatherArgs a, int gout_dtype, hipStream_t stream);
+hipError_t launch_gather_any(const GatherArgs &a, uint32_t grid, int gout_dtype, hipStream_t stream);
 
 // Zero every element of the (binary32) levels in `lv`; `numel[l]` and `dense[l]`
 // describe each level (dense levels are cleared as flat arrays).

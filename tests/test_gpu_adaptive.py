@@ -1,0 +1,158 @@
+"""GPU parity of RoIAlign at sampling ratios other than 2 on the 7x7 and 14x14 grids (the
+adaptive grid and fixed ratios) against the CPU oracle: the footprint forward and the tile
+gather that RE_BWD_AUTO takes with a plan, at the sizes where their panels and tiles end,
+with non-finite values, and with levels that are not the plan's.
+
+Tolerances are those of the other parity tests (gpu_helpers): a pixel's weight is a sum of
+at most 2 x 64 products of binary32 fractions, each correct to a few units of 2^-24, far
+inside 1e-5 of the result.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1906_07155_amd as rex
+from paper_1906_07155_amd import workloads as W
+from gpu_helpers import as_f64, check_bwd, check_fwd, from_device, log, to_device
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rex.lib()
+
+
+SHAPES = [(2, 70, 25, 90), (2, 70, 13, 45), (2, 70, 7, 23)]
+SCALES = [0.25, 0.125, 0.0625]
+
+
+def _setup(rois, shapes, scales, dt, layout, levels=None, seed=0):
+    rng = np.random.default_rng(seed)
+    feats = [rng.standard_normal(s, dtype=np.float32) for s in shapes]
+    if dt == "bf16":
+        feats = [W.f32_to_bf16_bits(f) for f in feats]
+    r = torch.from_numpy(rois).cuda()
+    dev = [to_device(f, dt, layout) for f in feats]
+    lv, ws = rex.plan(dev, scales, r, 56.0)
+    lv_np = oracle.level_map(rois, len(shapes), 56.0)
+    if levels is not None:
+        lv_np = np.asarray(levels(lv_np), np.int32)
+        lv = torch.from_numpy(lv_np).cuda()
+    return rng, feats, dev, r, lv, ws, lv_np
+
+
+def _run(name, rois, P, S, aligned=True, dt="f32", layout="cl", levels=None, zero_init=True,
+         shapes=SHAPES, scales=SCALES):
+    log("adaptive case %s: K=%d P=%d S=%d aligned=%d %s %s" % (
+        name, rois.shape[0], P, S, aligned, dt, layout))
+    rng, feats, dev, r, lv, ws, lv_np = _setup(rois, shapes, scales, dt, layout, levels)
+    K, C = rois.shape[0], shapes[0][1]
+    out = rex.roi_align_fwd(dev, scales, r, lv, (P, P), S, aligned, workspace=ws)
+    f64 = [as_f64(f, dt) for f in feats]
+    ref = oracle.roi_align_fwd(f64, scales, rois, lv_np, P, P, S, aligned, "parity")
+    check_fwd(from_device(out), ref, dt == "bf16", name + " forward")
+    g = rng.standard_normal((K, C, P, P), dtype=np.float32)
+    if dt == "bf16":
+        g = W.f32_to_bf16_bits(g)
+    g64 = as_f64(g, dt)
+    gref = oracle.roi_align_bwd(g64, shapes, scales, rois, lv_np, P, P, S, aligned, "parity")
+    aref = oracle.roi_align_bwd(np.abs(g64), shapes, scales, rois, lv_np, P, P, S, aligned,
+                                "parity")
+    grads = [torch.full(s, 7.0, dtype=torch.float32, device="cuda") for s in shapes]
+    if layout == "cl":
+        grads = [x.contiguous(memory_format=torch.channels_last) for x in grads]
+    rex.roi_align_bwd(to_device(g, dt, "nchw"), r, lv, (P, P), S, aligned, grads, scales,
+                      zero_init=zero_init, workspace=ws)
+    torch.cuda.synchronize()
+    base = 0.0 if zero_init else 7.0
+    for l in range(len(shapes)):
+        check_bwd(from_device(grads[l]) - base, gref[l], aref[l] + base * 2.0 ** -20 / 1e-4, False,
+                  "%s backward level %d" % (name, l))
+
+
+def _mixed_rois():
+    """Boxes of every size, among them one as wide as the map (two column panels), one as
+    tall, and boxes without width, outside the map and of an image that is not there."""
+    rng = np.random.default_rng(3)
+    rois = W.draw_rois(rng, 2, 17, (100, 360), (1.0, 300.0))
+    extra = np.array([[0, 0, 40, 360, 52], [1, 3, 0, 20, 100], [0, 30, 30, 30, 60],
+                      [1, 500, 20, 600, 50], [2, 10, 10, 60, 60], [0, -80, -60, 30, 25]], np.float32)
+    return np.concatenate([rois, extra])
+
+
+@pytest.mark.parametrize("S", [0, 1, 3, 4])
+@pytest.mark.parametrize("P", [7, 14])
+def test_sampling_ratios(P, S):
+    _run("ratios", _mixed_rois(), P, S, aligned=S != 3)
+
+
+@pytest.mark.parametrize("P", [7, 14])
+@pytest.mark.parametrize("dt,layout", [("bf16", "cl"), ("f32", "nchw"), ("bf16", "nchw")])
+def test_types_and_layouts(P, dt, layout):
+    _run("types", _mixed_rois(), P, 0, dt=dt, layout=layout, zero_init=layout == "cl")
+
+
+@pytest.mark.parametrize("C", [1, 3, 64, 129])
+def test_channels(C):
+    shapes = [(n, C, h, w) for n, _, h, w in SHAPES]
+    _run("channels", _mixed_rois(), 7, 0, shapes=shapes)
+
+
+def test_many_samples():
+    # one level: bins of up to 300 / 7 = 43 and 70 pixels (the grid is capped at 64 samples),
+    # so a wave's bin rows and the columns both take several panels
+    rois = np.array([[0, 0, 0, 300, 200], [0, 2, 1, 500, 190], [0, 5, 7, 40, 199]], np.float32)
+    _run("many", rois, 7, 0, shapes=[(1, 5, 200, 500)], scales=[1.0])
+
+
+def test_levels_not_the_plans():
+    # a caller's own levels: the tile lists hold the RoIs on the plan's levels only
+    _run("stray", _mixed_rois(), 7, 0, levels=lambda lv: (lv + (np.arange(lv.size) % 3 == 0)) % 3)
+
+
+def test_non_finite_feature():
+    # an infinity and a NaN reach exactly the bins whose samples read them
+    rois = _mixed_rois()
+    rng, feats, dev, r, lv, ws, lv_np = _setup(rois, SHAPES, SCALES, "f32", "cl")
+    feats[0][0, 3, 10, 40] = np.inf
+    feats[1][1, 69, 5, 20] = np.nan
+    dev = [to_device(f, "f32", "cl") for f in feats]
+    for P in (7, 14):
+        out = from_device(rex.roi_align_fwd(dev, SCALES, r, lv, (P, P), 0, True, workspace=ws))
+        ref = oracle.roi_align_fwd([f.astype(np.float64) for f in feats], SCALES, rois, lv_np, P, P,
+                                   0, True, "parity")
+        assert np.array_equal(np.isfinite(out), np.isfinite(ref))
+        ok = np.isfinite(ref)
+        check_fwd(np.where(ok, out, 0), np.where(ok, ref, 0), False, "non-finite feature")
+
+
+@pytest.mark.parametrize("zero_init", [True, False])
+@pytest.mark.parametrize("layout", ["cl", "nchw"])
+def test_non_finite_gradient(layout, zero_init):
+    # as the scatter: exactly the tapped pixels take the value
+    rois = _mixed_rois()
+    rng, feats, dev, r, lv, ws, lv_np = _setup(rois, SHAPES, SCALES, "f32", layout)
+    g = rng.standard_normal((rois.shape[0], 70, 7, 7), dtype=np.float32)
+    g[4, 2, 3, 3] = np.inf
+    g[20, 69, 0, 6] = np.nan
+    gd = torch.from_numpy(g).cuda()
+    res = []
+    for algo in ("auto", "scatter"):
+        grads = [torch.full(s, 7.0, dtype=torch.float32, device="cuda") for s in SHAPES]
+        if layout == "cl":
+            grads = [x.contiguous(memory_format=torch.channels_last) for x in grads]
+        rex.roi_align_bwd(gd, r, lv, (7, 7), 0, True, grads, SCALES, zero_init=zero_init,
+                          workspace=ws, algorithm=algo)
+        res.append([from_device(x) for x in grads])
+    for a, s in zip(*res):
+        assert np.array_equal(np.isfinite(a), np.isfinite(s))
+        assert np.array_equal(np.isnan(a), np.isnan(s))
+        ok = np.isfinite(s)
+        # the same products in two orders: 1e-4 of the sums' scale, as the gather against
+        # the oracle
+        assert np.all(np.abs(a[ok] - s[ok]) <= 1e-4 * np.maximum(np.abs(s[ok]), 1.0))
