@@ -256,7 +256,7 @@ hipError_t launch_deform_bwd(DeformArgs a, int feat_dtype, int gout_dtype, bool 
                              hipStream_t stream);
 
 // Greedy non-maximum suppression.
-constexpr int kNmsMaxBoxes = 8192;   // boxes per call: the sort's 64-bit items fill 64 KiB of LDS
+constexpr int kNmsMaxBoxes = 8192;   // boxes per call (the keys of the rank kernel in LDS)
 
 struct NmsArgs {
     const float *boxes;          // [N][4]
@@ -265,7 +265,7 @@ struct NmsArgs {
     int32_t *order;              // workspace: box index of every rank
     float4 *sboxes;              // workspace: boxes in rank order
     int32_t *scats;              // workspace: categories in rank order
-    uint64_t *mask;              // workspace: [N][nw] overlap bits of the upper triangle
+    uint64_t *mask;              // workspace, N * nw words: the overlaps (nms_lists, nms.hpp)
     int32_t *keep;               // [min(N, max_keep)]
     int32_t *num_keep;           // [1]
     int64_t max_keep;
