@@ -458,12 +458,16 @@ re_status_t box_nms(const float *boxes, const float *scores, const int32_t *cate
  *   num_boxes in [0, RE_MAX_NMS_BATCH_BOXES]; num_categories in [1, RE_MAX_NMS_CATEGORIES];
  *   iou_threshold, score_threshold not NaN; sigma finite > 0 (RE_NMS_GAUSSIAN);
  *   max_keep >= 0 with max_keep * num_categories < 2^31;
- *   workspace: device, 256-byte aligned, box_nms_batched_workspace_size() bytes (about
- *   48 bytes per box).
- * A category is handled by one workgroup: its candidates are sorted in LDS up to 8192
- * (above that in the workspace, slower); greedy selection tests blocks of 64 candidates
- * against the growing kept list, Soft-NMS runs one workgroup-wide iteration per
- * selection. */
+ *   workspace: device, 256-byte aligned, box_nms_batched_workspace_size() bytes: up to
+ *   2^18 boxes and 1024 categories about 48 bytes per box, at most 648 more per box
+ *   (16 MiB in all) for overlap lists and a few tables, beyond that 48 bytes per box.
+ *   A workspace of the 48 bytes per box alone is accepted too: the call then takes the
+ *   slower form below.
+ * Within those limits the whole GPU ranks the candidates and finds the overlaps, and a
+ * workgroup per category decides (greedy: all boxes whose overlaps are decided at once;
+ * Soft-NMS: one iteration per selection).  Beyond them, and for single categories past
+ * the room for their lists (greedy) or 4096 candidates (Soft-NMS), a category is sorted
+ * and walked in order by one workgroup.  Results are the same. */
 #define RE_NMS_HARD 0
 #define RE_NMS_LINEAR 1
 #define RE_NMS_GAUSSIAN 2

@@ -1156,7 +1156,9 @@ re_status_t box_nms(const float *boxes, const float *scores, const int32_t *cate
 
 namespace {
 struct NmsBatchLayout {
-    size_t count, start, sidx, skey, sbox, sscore, kbox, total;
+    size_t count, start, sidx, skey, sbox, sscore, kbox;
+    size_t least;   // a workspace of this size runs every category in one workgroup
+    size_t hist, bfirst, bcat, wfirst, words, total;
 };
 static NmsBatchLayout nmsb_layout(int64_t N, int32_t C) {
     NmsBatchLayout L{};
@@ -1168,7 +1170,16 @@ static NmsBatchLayout nmsb_layout(int64_t N, int32_t C) {
     L.sbox = L.skey + align256(n * 8);
     L.sscore = L.sbox + align256(n * 16);
     L.kbox = L.sscore + align256(n * 4);
-    L.total = L.kbox + align256(n * 16);
+    L.least = L.kbox + align256(n * 16);
+    L.total = L.hist = L.bfirst = L.bcat = L.wfirst = L.words = L.least;
+    if (sel_parallel(N, C)) {
+        const size_t c = static_cast<size_t>(C);
+        L.bfirst = L.hist + align256(static_cast<size_t>(kSelRanges) * c * 4);
+        L.bcat = L.bfirst + align256((c + 1) * 4);
+        L.wfirst = L.bcat + align256((n / 64 + c) * 4);
+        L.words = L.wfirst + align256(c * 4);
+        L.total = L.words + align256(static_cast<size_t>(sel_words(N)) * 8);
+    }
     return L;
 }
 static bool nmsb_sizes_ok(int64_t N, int32_t C) {
@@ -1206,7 +1217,7 @@ re_status_t box_nms_batched(const float *boxes, const float *scores, const int32
         return RE_ERR_INVALID_ARG;
     const NmsBatchLayout lay = nmsb_layout(num_boxes, num_categories);
     if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256) return RE_ERR_WORKSPACE;
-    if (workspace_bytes < lay.total) return RE_ERR_WORKSPACE;
+    if (workspace_bytes < lay.least) return RE_ERR_WORKSPACE;
     char *ws = static_cast<char *>(workspace);
     NmsBatchArgs a{};
     a.boxes = boxes;
@@ -1222,6 +1233,14 @@ re_status_t box_nms_batched(const float *boxes, const float *scores, const int32
     a.sbox = reinterpret_cast<float4 *>(ws + lay.sbox);
     a.sscore = reinterpret_cast<float *>(ws + lay.sscore);
     a.kbox = reinterpret_cast<float4 *>(ws + lay.kbox);
+    if (sel_parallel(num_boxes, num_categories) && workspace_bytes >= lay.total) {
+        a.hist = reinterpret_cast<int32_t *>(ws + lay.hist);
+        a.bfirst = reinterpret_cast<int32_t *>(ws + lay.bfirst);
+        a.bcat = reinterpret_cast<int32_t *>(ws + lay.bcat);
+        a.wfirst = reinterpret_cast<int32_t *>(ws + lay.wfirst);
+        a.words = reinterpret_cast<uint64_t *>(ws + lay.words);
+        a.word_cap = static_cast<int32_t>(sel_words(num_boxes));
+    }
     a.N = static_cast<int32_t>(num_boxes);
     a.C = num_categories;
     a.method = method;

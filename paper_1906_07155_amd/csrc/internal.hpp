@@ -325,12 +325,31 @@ struct NmsBatchArgs {
     float4 *sbox;                // [N] boxes in sorted order
     float *sscore;               // [N] scores in sorted order (Soft-NMS: current scores)
     float4 *kbox;                // [N] kept boxes of each category (greedy)
+    // the parallel selection's (null: the workspace does not hold them, or the sizes are past
+    // its limits)
+    int32_t *hist;               // [kSelRanges][C] candidates per range of boxes and category
+    int32_t *bfirst;             // [C + 1] first 64-candidate block of each category
+    int32_t *bcat;               // [N / 64 + C] category of each block
+    int32_t *wfirst;             // [C] first word of the category's overlap lists, -1: none
+    uint64_t *words;             // [word_cap] overlap lists (nms.hpp)
+    int32_t word_cap;
     int32_t N, C;
     int32_t method;
     int32_t max_keep;
     float iou_threshold, sigma, score_threshold;
-    int32_t pad;
 };
+
+// Limits of the parallel selection, and its room for overlap lists in 64-bit words: at most
+// 81 per candidate (one category of 8192), bounded at 16 MiB; categories past it are walked
+// in order.
+constexpr int kSelRanges = 32;
+constexpr int kSelMaxBoxes = 1 << 18;
+constexpr int kSelMaxCategories = 1024;
+constexpr int64_t kSelMaxWords = int64_t(1) << 21;
+inline bool sel_parallel(int64_t N, int32_t C) {
+    return N > 0 && N <= kSelMaxBoxes && C <= kSelMaxCategories;
+}
+inline int64_t sel_words(int64_t N) { return N * 81 < kSelMaxWords ? N * 81 : kSelMaxWords; }
 
 hipError_t launch_nms_batched(const NmsBatchArgs &a, hipStream_t stream);
 

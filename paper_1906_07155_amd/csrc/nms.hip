@@ -78,14 +78,14 @@ __global__ __launch_bounds__(kNmsRankThreads) void nms_rank_kernel(NmsArgs a) {
 __global__ __launch_bounds__(kNmsOverlapThreads) void nms_overlap_kernel(NmsArgs a, float share) {
     __shared__ int32_t count;
     overlap_rows(a.sboxes, a.scats, a.N, a.threshold, share, a.mask,
-                 static_cast<int>(blockIdx.x) / kNmsSplits,
-                 static_cast<int>(blockIdx.x) % kNmsSplits, &count);
+                 static_cast<int>(blockIdx.x) >> kNmsSplitLog,
+                 static_cast<int>(blockIdx.x) & ((1 << kNmsSplitLog) - 1), kNmsSplitLog, &count);
 }
 
 template <int M>
 __global__ __launch_bounds__(kNmsResolveThreads) void nms_resolve_kernel(NmsArgs a) {
     __shared__ ResolveSmem<M> sm;
-    resolve_rows<M>(a.mask, a.N, sm);
+    resolve_rows<M>(a.mask, a.N, kNmsSplitLog, sm);
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int nb = (a.N + 63) >> 6;
@@ -110,7 +110,7 @@ hipError_t launch_nms(NmsArgs a, hipStream_t stream) {
                           kNmsRankThreads, 0, stream>>>(a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        nms_overlap_kernel<<<static_cast<uint32_t>(a.nw * kNmsSplits), kNmsOverlapThreads, 0, stream>>>(
+        nms_overlap_kernel<<<static_cast<uint32_t>(a.nw << kNmsSplitLog), kNmsOverlapThreads, 0, stream>>>(
             a, nms_share(a.threshold));
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

@@ -23,12 +23,15 @@
 
 namespace rex {
 
-// The words of a row block are dealt to kNmsSplits workgroups (word w to split
-// w % kNmsSplits), and each writes a list of its own.
-constexpr int kNmsSplits = 8;
+// The words of a row block are dealt to 2^lg workgroups (word w to split w % 2^lg), and each
+// writes a list of its own: 8 in box_nms, whose one problem has at most 128 row blocks; 2 in
+// the selection, whose many categories fill the chip with fewer, longer workgroups (16
+// categories of 2000: 32 us with 8, 26 us with 2).
+constexpr int kNmsSplitLog = 3;
+constexpr int kSelSplitLog = 1;
 
 // Workspace of n boxes in nb blocks: the blocks' own words [n], the lists' lengths
-// [nb][kNmsSplits], and per list room for all of its words (64-bit) and their tags (16-bit,
+// [nb][2^lg], and per list room for all of its words (64-bit) and their tags (16-bit,
 // row in the block | word << 6).
 struct NmsLists {
     uint64_t *own;
@@ -38,11 +41,13 @@ struct NmsLists {
 };
 // Words of split s before the diagonal of block ib, those of the splits before it, and the
 // words of all lists before that of (ib, s).
-__host__ __device__ inline int32_t nms_split_words(int32_t ib, int32_t s) { return (ib + 7 - s) >> 3; }
-__host__ __device__ inline int32_t nms_list_base(int32_t n, int32_t ib, int32_t s) {
+__host__ __device__ inline int32_t nms_split_words(int32_t ib, int32_t s, int lg) {
+    return (ib + (1 << lg) - 1 - s) >> lg;
+}
+__host__ __device__ inline int32_t nms_list_base(int32_t n, int32_t ib, int32_t s, int lg) {
     const int32_t rows = n - 64 * ib < 64 ? n - 64 * ib : 64;
-    const int32_t r = ib & 7;
-    return 32 * ib * (ib - 1) + rows * (s * (ib >> 3) + (s < r ? s : r));
+    const int32_t r = ib & ((1 << lg) - 1);
+    return 32 * ib * (ib - 1) + rows * (s * (ib >> lg) + (s < r ? s : r));
 }
 __host__ __device__ inline int32_t nms_list_words(int32_t n) {
     const int32_t nb = (n + 63) >> 6;
@@ -51,7 +56,7 @@ __host__ __device__ inline int32_t nms_list_words(int32_t n) {
 // The lists' lengths in 64-bit words (a single block has no lists).
 __host__ __device__ inline int32_t nms_len_words(int32_t n) {
     const int32_t nb = (n + 63) >> 6;
-    return nb > 1 ? nb * (kNmsSplits / 2) : 0;
+    return nb > 1 ? nb << (kNmsSplitLog - 1) : 0;   // room for the most splits
 }
 // 64-bit words in all; never more than n * nb (the lists hold only half of the matrix).
 __host__ __device__ inline int64_t nms_words(int32_t n) {
@@ -81,7 +86,7 @@ __device__ __forceinline__ float overlap_part(float area, float c) {
     return c == c && !(area < 1e-30f) ? p : -__builtin_inff();
 }
 
-// Rows of block ib, words s, s + kNmsSplits, ... <= ib, by 512 threads: wave v takes rows 8 v
+// Rows of block ib, words s, s + 2^lg, ... <= ib, by 512 threads: wave v takes rows 8 v
 // .. 8 v + 7, whose boxes it holds in scalar registers, and walks the words with lane =
 // column box (the next word's boxes in flight); a compare writes the lanes' verdicts on a
 // row, the row's word, as a scalar mask.  The definition's division runs only for the rows
@@ -91,7 +96,7 @@ __device__ __forceinline__ float overlap_part(float area, float c) {
 constexpr int kNmsOverlapThreads = 512;
 __device__ __forceinline__ void overlap_rows(const float4 *boxes, const int32_t *cats, int n,
                                              float threshold, float share, uint64_t *ws, int ib,
-                                             int s, int32_t *count) {
+                                             int s, int lg, int32_t *count) {
     const int lane = threadIdx.x & 63;
     const int v = uniform_i(threadIdx.x >> 6);
     const int r0 = 8 * v;
@@ -100,7 +105,7 @@ __device__ __forceinline__ void overlap_rows(const float4 *boxes, const int32_t 
     if (threadIdx.x == 0) *count = 0;   // LDS: this list's length
     __syncthreads();
     const NmsLists out = nms_lists(ws, n);
-    const int32_t list = nms_list_base(n, ib, s);
+    const int32_t list = nms_list_base(n, ib, s, lg);
     float rx1[8], ry1[8], rx2[8], ry2[8], rarea[8], rpart[8];
     int32_t rcat[8];
     {
@@ -138,10 +143,10 @@ __device__ __forceinline__ void overlap_rows(const float4 *boxes, const int32_t 
     float4 nxt;
     int ncat;
     load(s, nxt, ncat);
-    for (int jb = s; jb <= ib; jb += kNmsSplits) {
+    for (int jb = s; jb <= ib; jb += 1 << lg) {
         const float4 bj = nxt;
         const int cj = ncat;
-        load(jb + kNmsSplits, nxt, ncat);
+        load(jb + (1 << lg), nxt, ncat);
         const bool jon = jb * 64 + lane < n;
         const float wj = bj.z - bj.x;
         const float hj = bj.w - bj.y;
@@ -192,7 +197,7 @@ __device__ __forceinline__ void overlap_rows(const float4 *boxes, const int32_t 
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0 && n > 64) out.len[ib * kNmsSplits + s] = *count;
+    if (threadIdx.x == 0 && n > 64) out.len[(ib << lg) + s] = *count;
 }
 
 // Up to M blocks per wave: n <= 1024 M boxes; kCap listed words in LDS (the rest, if any, are
@@ -207,7 +212,7 @@ struct ResolveSmem {
     uint64_t word[kCap];
     uint16_t col[kCap];          // the word's index
     uint16_t row[kCap];          // its box
-    int32_t first[16 * M * kNmsSplits + 1];   // each list's first entry
+    int32_t first[(16 * M << kNmsSplitLog) + 1];   // each list's first entry
     int32_t part[40];
 };
 
@@ -215,7 +220,7 @@ struct ResolveSmem {
 // blocks w, w + 16, ..., lane = box.
 constexpr int kNmsResolveThreads = 1024;
 template <int M>
-__device__ __forceinline__ void resolve_rows(uint64_t *ws, int n, ResolveSmem<M> &sm) {
+__device__ __forceinline__ void resolve_rows(uint64_t *ws, int n, int lg, ResolveSmem<M> &sm) {
     constexpr int kWaves = kNmsResolveThreads / 64;
     constexpr int kCap = ResolveSmem<M>::kCap;
     static_assert(kNmsResolveThreads == kPlanThreads, "block_exclusive_scan's workgroup");
@@ -223,7 +228,8 @@ __device__ __forceinline__ void resolve_rows(uint64_t *ws, int n, ResolveSmem<M>
     const int lane = tid & 63;
     const int wave = uniform_i(tid >> 6);
     const int nb = (n + 63) >> 6;
-    const int nl = nb > 1 ? nb * kNmsSplits : 0;
+    const int nl = nb > 1 ? nb << lg : 0;
+    const int sp = (1 << lg) - 1;
     const NmsLists in = nms_lists(ws, n);
     uint64_t own[M];
 #pragma unroll
@@ -239,7 +245,7 @@ __device__ __forceinline__ void resolve_rows(uint64_t *ws, int n, ResolveSmem<M>
     }
     // (a length is at most the list's room: block b's rows by its words)
     for (int l = tid; l < nl; l += kNmsResolveThreads)
-        sm.first[l] = max(0, min(in.len[l], 64 * nms_split_words(l >> 3, l & 7)));
+        sm.first[l] = max(0, min(in.len[l], 64 * nms_split_words(l >> lg, l & sp, lg)));
     __syncthreads();
     const int total = block_exclusive_scan(sm.first, nl, sm.part);
     if (tid == 0) sm.first[nl] = total;
@@ -252,11 +258,11 @@ __device__ __forceinline__ void resolve_rows(uint64_t *ws, int n, ResolveSmem<M>
             if (sm.first[mid] <= e) lo = mid;
             else hi = mid;
         }
-        const int at = nms_list_base(n, lo >> 3, lo & 7) + e - sm.first[lo];
+        const int at = nms_list_base(n, lo >> lg, lo & sp, lg) + e - sm.first[lo];
         const int t = in.tag[at];
         x = in.word[at];
-        w = min(t >> 6, lo >> 3);
-        i = min((lo >> 3) * 64 + (t & 63), n - 1);
+        w = min(t >> 6, lo >> lg);
+        i = min((lo >> lg) * 64 + (t & 63), n - 1);
     };
     const int held = min(total, kCap);
     for (int e0 = tid; e0 < held; e0 += 4 * kNmsResolveThreads) {

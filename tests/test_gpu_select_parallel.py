@@ -1,0 +1,81 @@
+"""GPU parity of box_nms_batched against the CPU oracle (exact) at the limits of its parallel
+form: category sizes around the blocks, the waves and registers of the Soft-NMS kernel and
+the overlap lists' room, and the calls that take the one-workgroup form instead (many
+categories, a workspace of the size that form needs)."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1906_07155_amd as rex
+from paper_1906_07155_amd import workloads as W
+from test_gpu_select import run
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _categories(sizes, seed, img=(300, 500), sides=(8.0, 150.0)):
+    """Boxes of categories of the given sizes, interleaved."""
+    rng = np.random.default_rng(seed)
+    b, s, _ = W.draw_proposals(rng, 1, int(sum(sizes)), img, sides, 0.5)
+    c = np.repeat(np.arange(len(sizes), dtype=np.int32), sizes)
+    return b, s, rng.permutation(c)
+
+
+SIZES = [1, 63, 64, 65, 128, 129, 0, 255, 256, 257, 320, 511, 512, 513, 1024, 1025]
+
+
+@pytest.mark.parametrize("method", ["hard", "linear", "gaussian"])
+@pytest.mark.parametrize("max_keep", [40, 1500])
+def test_sizes(method, max_keep):
+    b, s, c = _categories(SIZES, 1)
+    s[::5] = s[2::5][:s[::5].size]                  # equal scores
+    run("sizes " + method, b, s, c, len(SIZES), method, thr=0.4, sigma=0.5,
+        st=0.01 if method != "hard" else float("-inf"), max_keep=max_keep)
+
+
+@pytest.mark.parametrize("method", ["hard", "linear"])
+def test_registers_and_list_room(method):
+    # 4096 candidates fill the Soft-NMS registers, one more takes the walk in order; four
+    # categories of 8192 exceed the room of the overlap lists (three fit)
+    sizes = [8192] * 4 if method == "hard" else [2049, 4096, 4097]
+    b, s, c = _categories(sizes, 2, img=(800, 1333), sides=(4.0, 80.0))
+    run("room " + method, b, s, c, len(sizes), method, thr=0.5, st=0.0, max_keep=150)
+
+
+@pytest.mark.parametrize("method", ["hard", "linear", "gaussian"])
+def test_one_workgroup_form(method):
+    b, s, c = _categories(SIZES, 3)
+    st = 0.01 if method != "hard" else float("-inf")
+    # more categories than the parallel form takes
+    run("1025 categories", b, s, c, 1025, method, thr=0.4, st=st, max_keep=20)
+    # a workspace of the size the one-workgroup form needs: 48 bytes per box and the
+    # categories' counters, each array rounded up to 256 bytes
+    n, C = s.shape[0], len(SIZES)
+    up = lambda x: (x + 255) // 256 * 256
+    least = up(4 * C) + up(4 * C + 4) + 2 * up(4 * n) + up(8 * n) + 2 * up(16 * n)
+    ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+    dev = [torch.from_numpy(x).cuda() for x in (b, s, c)]
+    args = (C, method, 0.4, 0.5, st, 200)
+    got = rex.box_nms_batched(*dev, *args, workspace=ws)
+    ref = oracle.nms_batched(b, s, c, *args)
+    for g, r in zip(got, ref):
+        assert np.array_equal(g.cpu().numpy().view(np.uint32), r.view(np.uint32))
+    with pytest.raises(rex.RoIExtractError):
+        rex.box_nms_batched(*dev, *args, workspace=ws[:least - 256])
+
+
+@pytest.mark.parametrize("method", ["linear", "gaussian"])
+def test_infinite_scores(method):
+    # inf * 0 is NaN, which is selected last and never dropped
+    b, s, c = _categories([300, 700], 4)
+    s[::9] = np.inf
+    b[1::9] = b[::9][:b[1::9].shape[0]]
+    run("infinite " + method, b, s, c, 2, method, thr=-0.5, sigma=0.1, st=0.2, max_keep=900)
