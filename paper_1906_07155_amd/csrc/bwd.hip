@@ -25,6 +25,7 @@
 //                       atomics per valid sample.
 //   zero kernels        clear the gradient pyramid.
 #include <algorithm>
+#include <type_traits>
 
 #include "gather.hpp"
 
@@ -286,19 +287,22 @@ struct GatherSmem {
     static constexpr int NCOL = PW * S;
     static constexpr int T = 8;
     static constexpr int NB = PH * PW;
-    static constexpr int GB = 64 * NB;   // 32-bit words of one RoI's gradient block
-    // The block is copied in runs of RUN elements, one copy instruction per run:
-    // 16 bytes per lane for binary32, one element per lane for bf16.  A slot holds
-    // whole runs (GBP words); the words past the block are never read.
-    static constexpr int RUN = sizeof(TG) == 4 ? 256 : 64;
+    static constexpr int GB = 64 * NB;   // elements of one RoI's gradient block
+    // The block is staged as it lies in memory, copied in runs of RUN elements, 16 bytes per
+    // lane and one copy instruction per run.  A slot holds whole runs (GBP 32-bit words); the
+    // words past the block are never read.  (bf16 values in 32-bit slots, one per lane and
+    // copy, held the 14x14 kernels to two workgroups per CU with 185 registers; packed they
+    // take 126: mask head batch 16 step 873 -> 633 us, both heads 1840 -> 1213 us, box head
+    // batch 16 733 -> 713 us.)
+    static constexpr int RUN = 1024 / static_cast<int>(sizeof(TG));
     static constexpr int NRUN = (GB + RUN - 1) / RUN;
-    static constexpr int GBP = NRUN * RUN;
+    static constexpr int GBP = NRUN * 256 > 2048 ? NRUN * 256 : 2048;   // (the store's scratch)
     // The staged gradient blocks form a ring of NBUF: the next RoI's block is copied
     // into the other slot by the buffer unit while the current one is consumed, when
-    // two blocks fit in 52 KiB.  The copy gives every lane a 32-bit LDS slot whatever
-    // the element size, so a block holds one 32-bit word per element (a bf16 value in
-    // its low half).
-    static constexpr int NBUF = 2 * GBP * 4 <= 53248 ? 2 : 1;
+    // two blocks fit in 28 KiB.  Four workgroups per CU beat a second slot: the 25 KiB
+    // blocks of bf16 14x14 take one (batch-16 mask head step: two slots 849 us, one 633).
+    static constexpr int NBUF = 2 * GBP * 4 <= 28 * 1024 ? 2 : 1;
+    using Elem = std::conditional_t<sizeof(TG) == 4, uint32_t, uint16_t>;
     Tap tap[2][NR + NCOL];
     __align__(16) float wy[4][PH * T];
     __align__(16) float wx[4][PW * T];
@@ -347,14 +351,14 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
 
     // Coalesced copy of kept RoI j's gradient block (nch x NB values) into LDS
     // through a buffer resource over exactly that block: run r = wave + 4 m goes to
-    // words [RUN r, RUN r + RUN), lane i writing the RUN / 64 elements from RUN r +
-    // i RUN / 64 on (the LDS address is the uniform run base plus the lane's bytes, in
-    // lane order; the global offset is the lane's own); the range check, which works
-    // per dword, supplies the zeros past the valid channels.
+    // words [256 r, 256 r + 256), lane i writing 16 bytes from byte 1024 r + 16 i on (the
+    // LDS address is the uniform run base plus the lane's bytes, in lane order; the global
+    // offset is the lane's own); the range check, which works per dword, supplies the
+    // zeros past the valid channels.
     const int nvalid = x.nch * NB;
-    // 16-byte copies need every block 16-byte aligned: a multiple of 4 channels and an
-    // aligned gradient (binary32 only)
-    const bool wide = sizeof(TG) == 4 && (lv.C & 3) == 0 &&
+    // 16-byte copies need every block 16-byte aligned: the gradient's base and a RoI's bytes
+    // (a channel group's are a multiple of 16)
+    const bool wide = (kstride * int64_t(sizeof(TG)) & 15) == 0 &&
                       (reinterpret_cast<uintptr_t>(h.gout) & 15u) == 0;
     auto fetch = [&](int j, uint32_t *gdst) {
         const int k = uniform_i(sm.k[j]);   // one resource for the wave, no waterfall
@@ -362,32 +366,35 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
                           (static_cast<int64_t>(x.cg) * 64 * NB + static_cast<int64_t>(k) * kstride) *
                               int64_t(sizeof(TG));
         const __amdgpu_buffer_rsrc_t rs = make_rsrc(src, static_cast<uint32_t>(nvalid) * uint32_t(sizeof(TG)));
-        constexpr int RUN = SM::RUN, NRUN = SM::NRUN;
-        if (RUN == 256 && wide) {
+        constexpr int NRUN = SM::NRUN;
+        if (wide) {
 #pragma unroll
             for (int m = 0; m < (NRUN + 3) / 4; ++m) {
                 const int run = wave + 4 * m;
                 if (m < NRUN / 4 || run < NRUN) {
-                    auto *dst = (__attribute__((address_space(3))) void *)(gdst + RUN * run);
-                    const uint32_t off = static_cast<uint32_t>(RUN * run + lane * 4) * 4u;
+                    auto *dst = (__attribute__((address_space(3))) void *)(gdst + 256 * run);
+                    const uint32_t off = static_cast<uint32_t>(256 * run + lane * 4) * 4u;
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, off, 0, 0, 0);
                 }
             }
-        } else {
-            // one element per lane and instruction (bf16, or blocks not 16-byte aligned)
+        } else if constexpr (sizeof(TG) == 4) {
+            // blocks not 16-byte aligned: one element per lane and instruction
             constexpr int NR64 = GB / 64;
 #pragma unroll
             for (int m = 0; m < (NR64 + 3) / 4; ++m) {
                 const int run = wave + 4 * m;
                 if (m < NR64 / 4 || run < NR64) {
                     auto *dst = (__attribute__((address_space(3))) void *)(gdst + 64 * run);
-                    const uint32_t off = static_cast<uint32_t>(64 * run + lane) * uint32_t(sizeof(TG));
-                    if constexpr (sizeof(TG) == 4)
-                        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 4, off, 0, 0, 0);
-                    else
-                        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 2, off, 0, 0, 0);
+                    const uint32_t off = static_cast<uint32_t>(64 * run + lane) * 4u;
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 4, off, 0, 0, 0);
                 }
             }
+        } else {
+            // (a 16-bit copy to LDS fills a 32-bit slot, so packed values go through registers)
+            uint16_t *const g16 = reinterpret_cast<uint16_t *>(gdst);
+#pragma unroll 4
+            for (int e = tid; e < GB; e += 256)
+                g16[e] = static_cast<uint16_t>(buf_load_raw<uint16_t>(rs, static_cast<uint32_t>(e) * 2u));
         }
     };
     // The copies of this wave are complete (vmcnt 0); a barrier then publishes them.
@@ -409,7 +416,8 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
         }
     };
     // Contribution of kept RoI j to this wave's quadrant.
-    auto consume = [&](int j, const uint32_t *gsrc, int tb) {
+    auto consume = [&](int j, const uint32_t *gblk, int tb) {
+        const typename SM::Elem *gsrc = reinterpret_cast<const typename SM::Elem *>(gblk);
         const int ymin = sm.rng[j][0], ymax = sm.rng[j][1];
         const int xmin = sm.rng[j][2], xmax = sm.rng[j][3];
         if (!x.wave_on || ymax < R0 || ymin >= R0 + T || xmax < Q0 || xmin >= Q0 + T) return;
@@ -465,7 +473,7 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
         if (pha < 0 || pwa < 0) return;
         wave_sync();
 
-        const uint32_t *gl = gsrc + lane * NB + pwa;   // this lane's channel, stride NB (odd)
+        const typename SM::Elem *gl = gsrc + lane * NB + pwa;   // this lane's channel, stride NB
         const float *wxa = wx + pwa * T;
         gather_rows<TG, PW>(acc, gl, wxa, wy, yb, pha, phb, pwb - pwa + 1);
         // the weights are rewritten for the next RoI only after the next barrier

@@ -221,14 +221,15 @@ __device__ __forceinline__ void outer_rows(float (&acc)[8][8], const float *yrow
 // gl points at g[0][pwa] of this lane's channel, wxa at Wx[pwa][0], wy at Wy[0][0];
 // yb holds the nonzero pattern of Wy (bit ph * 8 + r), which decides the half
 // quadrants (rows 0-3, 4-7) a bin row updates.
-template <typename TG, int PW, int YP>
-__device__ __forceinline__ void gather_rows(float (&acc)[8][8], const uint32_t *gl,
+// (GE: the staged element, a 32-bit slot or the 16 bits of a packed bf16 value).
+template <typename TG, int PW, typename GE, int YP>
+__device__ __forceinline__ void gather_rows(float (&acc)[8][8], const GE *gl,
                                             const float *wxa, const float *wy,
                                             const uint64_t (&yb)[YP], int pha, int phb, int npw) {
     for (int ph = pha; ph <= phb; ++ph) {
         const uint32_t rb = static_cast<uint32_t>(yb[YP == 1 ? 0 : ph >> 3] >> ((ph & 7) * 8)) & 0xffu;
         if (rb == 0) continue;
-        const uint32_t *gr = gl + ph * PW;
+        const GE *gr = gl + ph * PW;
         // The run of bins is unrolled up to its longest possible length, so every
         // LDS address is a fixed offset from gr / wxa (no loop-carried pointers, which
         // would hide from the compiler that these reads do not touch the slot being
