@@ -32,16 +32,15 @@ namespace rex {
 #ifndef REX_FWD_CX
 #define REX_FWD_CX 8
 #endif
-// channels per workgroup of the NCHW kernel (7x7, 14x14 grids): the kernel waits on
-// dependent loads, so more resident workgroups (less LDS each) beat fewer, fuller ones
-// (batch-2 box head: 2 channels 244 us, 4: 164, 8: 183, 16: 260; mask head 1 or 2: 138,
-// 146)
-#ifndef REX_NCHW_CC7
-#define REX_NCHW_CC7 4
-#endif
-#ifndef REX_NCHW_CC14
-#define REX_NCHW_CC14 1
-#endif
+// Channels staged at a time by the NCHW kernel (7x7, 14x14 grids), the most chunks of them a
+// workgroup takes, and the workgroups a launch keeps before it gives them more than one
+// (batch-2 box head with the plan, fp32 / bf16: one chunk of 4 per workgroup 161 / 178 us;
+// runs of 16 chunks of 4 channels 120 / 188, of 2 115 / 135, of 1 136 / 148; runs of 8
+// chunks of 2 118 / 141, of 32 127 / 149.  Mask head, one channel: 131 -> 87 us.)
+constexpr int kNchwCC7 = 2;
+constexpr int kNchwCC14 = 1;
+constexpr int kNchwRun = 16;
+constexpr int kNchwWorkgroups = 4096;
 // columns per load unit and units in flight with two bf16 channels per lane (7x7 grid)
 #ifndef REX_FWD_CX2_BF16
 #define REX_FWD_CX2_BF16 4
@@ -630,6 +629,10 @@ static hipError_t launch_fwd_cl(FwdArgs a, hipStream_t stream) {
     return hipGetLastError();
 }
 
+static bool nchw_offsets_fit(const LevelTable &t, int cc);
+template <typename T, typename TO, int PH, int PW, int CC>
+static hipError_t launch_fwd_nchw(FwdArgs a, hipStream_t stream);
+
 template <typename T, typename TO>
 static hipError_t launch_fwd_typed(FwdArgs a, bool fast, hipStream_t stream) {
     // a dispatch holds fewer than 2^32 work-items; beyond that, the strided kernel
@@ -662,9 +665,10 @@ static hipError_t launch_fwd_typed(FwdArgs a, bool fast, hipStream_t stream) {
         return launch_fwd_cl<T, TO, 14, 14, 4, 16, 1>(a, stream);
     }
     // other layouts (channels in separate planes): the staged kernel on the same grids
-    if (fwd_fast_available(a.PH, a.PW, a.S) && static_cast<int64_t>(a.K) * a.lv.C < (int64_t(1) << 30)) {
-        if (a.PH == 7) return launch_fwd_nchw<T, TO, 7, 7, REX_NCHW_CC7>(a, stream);
-        return launch_fwd_nchw<T, TO, 14, 14, REX_NCHW_CC14>(a, stream);
+    if (fwd_fast_available(a.PH, a.PW, a.S) && static_cast<int64_t>(a.K) * a.lv.C < (int64_t(1) << 30) &&
+        nchw_offsets_fit(a.lv, kNchwCC7)) {
+        if (a.PH == 7) return launch_fwd_nchw<T, TO, 7, 7, kNchwCC7>(a, stream);
+        return launch_fwd_nchw<T, TO, 14, 14, kNchwCC14>(a, stream);
     }
     const int64_t total = static_cast<int64_t>(a.K) * a.lv.C * a.PH * a.PW;
     const int64_t blocks = std::min<int64_t>((total + 255) / 256, 16384);
@@ -676,16 +680,16 @@ static hipError_t launch_fwd_typed(FwdArgs a, bool fast, hipStream_t stream) {
 // Channels in separate planes (NCHW): staged footprint, lanes along x
 // ---------------------------------------------------------------------------
 //
-// One workgroup per (RoI, CC channels).  The sample positions of an axis grow with
-// the sample index, so the tap rows (columns) form runs of equal `lo`, each adding
+// One workgroup per (RoI, run of chunks of CC channels).  The sample positions of an axis
+// grow with the sample index, so the tap rows (columns) form runs of equal `lo`, each adding
 // `lo` and, unless it is the next run's `lo` or the map edge, `lo + 1` to the
 // distinct set: one wave lists the distinct rows and gives every sample the indices
 // of its two taps in the list (a scan over the run ends).  The workgroup then loads
-// every channel's distinct rows x distinct columns into LDS with consecutive lanes
+// a chunk's distinct rows x distinct columns into LDS with consecutive lanes
 // on consecutive columns (a RoI's columns are a contiguous run unless its bins are
 // wider than a pixel), reduces each tap row along x per bin column, and the tap
-// rows along y per bin.  Any other grid, or a RoI whose taps are not monotone, takes
-// the per-output path.
+// rows along y per bin, the next chunk's loads in flight.  Any other grid, or a RoI whose
+// taps are not monotone, takes the per-output path.
 template <int N>
 struct NchwAxis {
     int idx_lo[N], idx_hi[N];   // per sample: its taps' positions in the distinct list
@@ -731,26 +735,60 @@ template <int PH, int PW, int CC>
 struct NchwSmem {
     static constexpr int S = 2;
     static constexpr int NR = PH * S, NCOL = PW * S;
+    static constexpr int FW = CC * 2 * NR * 2 * NCOL, RW = CC * 2 * NR * PW;
     NchwAxis<NR> y;
     NchwAxis<NCOL> x;
-    float fw[CC * 2 * NR * 2 * NCOL];   // [channel][distinct row][distinct column]
-    float rw[CC * 2 * NR * PW];         // [channel][distinct row][bin column]
+    float fw[FW + 1];   // [channel][distinct row][distinct column], then a zero
+    float rw[RW + 1];   // [channel][distinct row][bin column], then a zero
 };
+
+// Two samples of a bin as four staged values and their weights: a sample off the map reads
+// the zero element at `zero` (its own taps are not read, whatever their values).
+struct NchwPair {
+    uint32_t at0, at1;   // lo | hi << 16 of each sample
+    float l0, h0, l1, h1;
+};
+template <int N>
+__device__ __forceinline__ NchwPair nchw_pair(const NchwAxis<N> &a, int bin, int base, int pitch,
+                                              int zero) {
+    NchwPair p;
+    const int u = 2 * bin;
+    const bool v0 = a.idx_lo[u] >= 0, v1 = a.idx_lo[u + 1] >= 0;
+    const int z = zero | zero << 16;
+    p.at0 = static_cast<uint32_t>(v0 ? (base + a.idx_lo[u] * pitch) | (base + a.idx_hi[u] * pitch) << 16 : z);
+    p.at1 = static_cast<uint32_t>(
+        v1 ? (base + a.idx_lo[u + 1] * pitch) | (base + a.idx_hi[u + 1] * pitch) << 16 : z);
+    p.l0 = a.w_lo[u];
+    p.h0 = a.w_hi[u];
+    p.l1 = a.w_lo[u + 1];
+    p.h1 = a.w_hi[u + 1];
+    return p;
+}
+__device__ __forceinline__ float nchw_sum(const NchwPair &p, const float *v) {
+    float acc = p.l0 * v[p.at0 & 0xffffu];
+    acc = fmaf(p.h0, v[p.at0 >> 16], acc);
+    acc = fmaf(p.l1, v[p.at1 & 0xffffu], acc);
+    return fmaf(p.h1, v[p.at1 >> 16], acc);
+}
 
 template <typename T, typename TO, int PH, int PW, int CC>
 __global__ __launch_bounds__(256) void fwd_nchw_kernel(FwdArgs a) {
     constexpr int S = 2;
     using SM = NchwSmem<PH, PW, CC>;
-    constexpr int NR = SM::NR, NCOL = SM::NCOL;
+    constexpr int NR = SM::NR, NCOL = SM::NCOL, NB = PH * PW;
+    constexpr int NLOAD = (SM::FW + 255) / 256;   // staged values per thread
+    constexpr int NX = (SM::RW + 255) / 256;      // row sums per thread
+    static_assert(CC * NB <= 256 && SM::FW < 0x10000, "one output per thread, 16-bit indices");
     __shared__ SM sm;
     const FwdArgs &ka = *(const FwdArgs *)__builtin_amdgcn_kernarg_segment_ptr();
     const LevelTable &lv = ka.lv;
-    // channel chunk outer, plan order inner: neighbouring workgroups read the same
+    // run of channel chunks outer, plan order inner: neighbouring workgroups read the same
     // planes around neighbouring RoIs
     const uint32_t lid = xcd_remap(blockIdx.x, gridDim.x);
-    const int chunk = static_cast<int>(lid / static_cast<uint32_t>(ka.K));
-    const int slot = static_cast<int>(lid) - chunk * ka.K;
-    const int c0 = chunk * CC;
+    const int group = static_cast<int>(lid / static_cast<uint32_t>(ka.K));
+    const int slot = static_cast<int>(lid) - group * ka.K;
+    const int c0 = group * ka.spw * CC;                       // the workgroup's channels
+    const int c1 = min(lv.C, c0 + ka.spw * CC);
     int k = uniform_i(ka.perm ? ka.perm[slot] : slot);
     const bool kvalid = k >= 0 && k < ka.K;
     if (!kvalid) k = 0;
@@ -767,17 +805,20 @@ __global__ __launch_bounds__(256) void fwd_nchw_kernel(FwdArgs a) {
     const Axis ay = axis_setup(y1, y2, L.scale, ka.aligned, PH, S);
     if (wave == 0) nchw_axis<NR, S>(ay, L.H, active, sm.y);
     else if (wave == 1) nchw_axis<NCOL, S>(ax, L.W, active, sm.x);
+    else if (t == 128) {
+        sm.fw[SM::FW] = 0.0f;
+        sm.rw[SM::RW] = 0.0f;
+    }
     __syncthreads();
     const int nr = sm.y.n, nc = sm.x.n;
-    const int nch = min(CC, lv.C - c0);
-    const int64_t kout = static_cast<int64_t>(k) * lv.C * PH * PW;
+    const int64_t kout = static_cast<int64_t>(k) * lv.C * NB;
     constexpr float inv_count = 1.0f / static_cast<float>(S * S);
     if (!kvalid) return;   // a plan slot past the RoIs (never with a valid plan)
 
     if (sm.y.bad || sm.x.bad) {
         // taps out of order (binary32 ties): each output from its own samples
-        for (int e = t; e < nch * PH * PW; e += 256) {
-            const int c = e / (PH * PW), j = e - c * (PH * PW);
+        for (int e = t; e < (c1 - c0) * NB; e += 256) {
+            const int c = e / NB, j = e - c * NB;
             const int ph = j / PW, pw = j - ph * PW;
             float sum = 0.0f;
             if (active) {
@@ -795,78 +836,90 @@ __global__ __launch_bounds__(256) void fwd_nchw_kernel(FwdArgs a) {
                     }
                 }
             }
-            store_f32(as_global_mut<TO>(ka.out) + kout + static_cast<int64_t>(c0) * PH * PW + e,
+            store_f32(as_global_mut<TO>(ka.out) + kout + static_cast<int64_t>(c0) * NB + e,
                       sum * inv_count);
         }
         return;
     }
 
-    // a4: the footprint of every channel of the chunk, eight loads in flight per lane
+    // What this thread stages, sums along x and along y is the same for every chunk: the
+    // offsets, indices and weights are worked out once and kept in registers.
     const int per_c = nr * nc;
-    const int nload = nch * per_c;
-    const gcptr<T> img = as_global<T>(L.data) + b * L.sn + static_cast<int64_t>(c0) * L.sc;
-    for (int e0 = t; e0 < nload; e0 += 8 * 256) {
-        float v[8];
+    int32_t off[NLOAD];   // element offset in the chunk's planes (the host bounds it), -1: none
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int e = e0 + u * 256;
-            v[u] = 0.0f;
-            if (e < nload) {
-                const int c = small_div_exact(e, per_c);
-                const int rem = e - c * per_c;
-                const int j = small_div_exact(rem, nc);
-                const int i = rem - j * nc;
-                v[u] = load_f32(img + c * L.sc + sm.y.list[j] * L.sh + sm.x.list[i] * L.sw);
-            }
+    for (int u = 0; u < NLOAD; ++u) {
+        const int e = t + u * 256;
+        off[u] = -1;
+        if (e < CC * per_c) {
+            const int c = small_div_exact(e, per_c);
+            const int rem = e - c * per_c;
+            const int j = small_div_exact(rem, nc);
+            const int i = rem - j * nc;
+            off[u] = static_cast<int32_t>(c * L.sc + sm.y.list[j] * L.sh + sm.x.list[i] * L.sw);
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (e0 + u * 256 < nload) sm.fw[e0 + u * 256] = v[u];
     }
-    __syncthreads();
-    // along x: every distinct tap row of every channel, per bin column
-    const int nx = nch * nr * PW;
-    for (int e = t; e < nx; e += 256) {
-        const int cj = small_div_exact(e, PW);          // channel * nr + row
-        const int pw = e - cj * PW;
-        const float *row = sm.fw + cj * nc;
-        float acc = 0.0f;
+    NchwPair px[NX];
 #pragma unroll
-        for (int ix = 0; ix < S; ++ix) {
-            const int u = pw * S + ix;
-            const int il = sm.x.idx_lo[u];
-            if (il < 0) continue;   // off the map: no contribution
-            acc = fmaf(sm.x.w_lo[u], row[il], acc);
-            acc = fmaf(sm.x.w_hi[u], row[sm.x.idx_hi[u]], acc);
-        }
-        sm.rw[e] = acc;
+    for (int u = 0; u < NX; ++u) {
+        const int e = t + u * 256;
+        const int cj = small_div_exact(e, PW);   // channel * nr + row
+        px[u] = nchw_pair(sm.x, e - cj * PW, cj < CC * nr ? cj * nc : 0, 1, SM::FW);
     }
-    __syncthreads();
-    // along y: every bin, then the output (written in order, one channel's bins
-    // contiguous)
-    for (int e = t; e < nch * PH * PW; e += 256) {
-        const int c = small_div_exact(e, PH * PW);
-        const int jj = e - c * (PH * PW);
+    NchwPair py;
+    {
+        const int c = small_div_exact(min(t, CC * NB - 1), NB);
+        const int jj = min(t, CC * NB - 1) - c * NB;
         const int ph = small_div_exact(jj, PW);
-        const int pw = jj - ph * PW;
-        const float *col = sm.rw + c * nr * PW + pw;
-        float acc = 0.0f;
+        py = nchw_pair(sm.y, ph, c * nr * PW + jj - ph * PW, PW, SM::RW);
+    }
+    gcptr<T> src = as_global<T>(L.data) + (active ? b * L.sn : 0) + static_cast<int64_t>(c0) * L.sc;
+    float v[NLOAD];
+    auto load = [&](int c) {   // the chunk of channels from c on
+        const int n = min(CC, c1 - c) * per_c;
 #pragma unroll
-        for (int iy = 0; iy < S; ++iy) {
-            const int u = ph * S + iy;
-            const int il = sm.y.idx_lo[u];
-            if (il < 0) continue;
-            acc = fmaf(sm.y.w_lo[u], col[il * PW], acc);
-            acc = fmaf(sm.y.w_hi[u], col[sm.y.idx_hi[u] * PW], acc);
-        }
-        store_f32(as_global_mut<TO>(ka.out) + kout + static_cast<int64_t>(c0) * PH * PW + e,
-                  acc * inv_count);
+        for (int u = 0; u < NLOAD; ++u)
+            v[u] = t + u * 256 < n ? load_f32(src + off[u]) : 0.0f;
+        src += CC * L.sc;
+    };
+    load(c0);
+    for (int c = c0; c < c1; c += CC) {
+        const int nch = min(CC, c1 - c);
+#pragma unroll
+        for (int u = 0; u < NLOAD; ++u)
+            if (off[u] >= 0) sm.fw[t + u * 256] = v[u];
+        __syncthreads();
+        if (c + CC < c1) load(c + CC);   // in flight while this chunk is summed
+#pragma unroll
+        for (int u = 0; u < NX; ++u)
+            if (t + u * 256 < nch * nr * PW) sm.rw[t + u * 256] = nchw_sum(px[u], sm.fw);
+        __syncthreads();
+        if (t < nch * NB)
+            store_f32(as_global_mut<TO>(ka.out) + kout + static_cast<int64_t>(c) * NB + t,
+                      nchw_sum(py, sm.rw) * inv_count);
     }
 }
 
+// Every staged offset of a chunk fits 31 bits (a plane of more than 2^29 elements, or as
+// large a stride, takes the general kernel).
+static bool nchw_offsets_fit(const LevelTable &t, int cc) {
+    for (int l = 0; l < t.num; ++l) {
+        const LevelArg &v = t.l[l];
+        if (static_cast<double>(cc - 1) * v.sc + static_cast<double>(v.H - 1) * v.sh +
+                static_cast<double>(v.W - 1) * v.sw >= 2147483648.0)
+            return false;
+    }
+    return true;
+}
+
 template <typename T, typename TO, int PH, int PW, int CC>
-static hipError_t launch_fwd_nchw(const FwdArgs &a, hipStream_t stream) {
-    const int64_t grid = static_cast<int64_t>(a.K) * ((a.lv.C + CC - 1) / CC);
+static hipError_t launch_fwd_nchw(FwdArgs a, hipStream_t stream) {
+    // Chunks per workgroup: the geometry (divisions, scans, index tables) costs as much as
+    // several chunks, so a workgroup takes up to kNchwRun of them while kNchwWorkgroups
+    // remain.
+    const int64_t chunks = (a.lv.C + CC - 1) / CC;
+    a.spw = static_cast<int32_t>(
+        std::max<int64_t>(1, std::min<int64_t>({chunks, kNchwRun, a.K * chunks / kNchwWorkgroups})));
+    const int64_t grid = static_cast<int64_t>(a.K) * ((chunks + a.spw - 1) / a.spw);
     if (grid >= (int64_t(1) << 31)) return hipErrorInvalidConfiguration;
     fwd_nchw_kernel<T, TO, PH, PW, CC><<<static_cast<uint32_t>(grid), 256, 0, stream>>>(a);
     return hipGetLastError();
