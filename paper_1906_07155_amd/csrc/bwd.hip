@@ -287,7 +287,17 @@ struct GatherSmem {
     static constexpr int NCOL = PW * S;
     static constexpr int T = 8;
     static constexpr int NB = PH * PW;
-    static constexpr int GB = 64 * NB;   // elements of one RoI's gradient block
+    // Bin rows staged at a time: all of them, except for binary32 14x14, whose 50 KiB block
+    // held the kernel to two workgroups per CU (mask head batch 2 step 136 us, 122-132 in parts;
+    // box and mask heads of batch 2 307 -> 252 us): an item of the walk is then one part of
+    // a RoI, 8 or 6 bin rows, with its own tap extent (part 1 starts 448 bytes into a
+    // channel's 784, on 16 bytes as every channel does).  A channel's part takes PITCH
+    // elements of the slot.
+    static constexpr int RP = sizeof(TG) == 4 && PH == 14 ? 8 : PH;
+    static constexpr int NPART = (PH + RP - 1) / RP;
+    static constexpr int PITCH = NPART == 1 ? NB : RP * PW + 4;
+    static constexpr int ITEMS = 64 * NPART;
+    static constexpr int GB = 64 * PITCH;   // elements of one staged block
     // The block is staged as it lies in memory, copied in runs of RUN elements, 16 bytes per
     // lane and one copy instruction per run.  A slot holds whole runs (GBP 32-bit words); the
     // words past the block are never read.  (bf16 values in 32-bit slots, one per lane and
@@ -304,11 +314,11 @@ struct GatherSmem {
     static constexpr int NBUF = 2 * GBP * 4 <= 28 * 1024 ? 2 : 1;
     using Elem = std::conditional_t<sizeof(TG) == 4, uint32_t, uint16_t>;
     Tap tap[2][NR + NCOL];
-    __align__(16) float wy[4][PH * T];
+    __align__(16) float wy[4][RP * T];
     __align__(16) float wx[4][PW * T];
-    int k[64];
-    float ax[64][4];
-    int rng[64][4];   // per kept RoI: tap extent ymin, ymax, xmin, xmax
+    int k[ITEMS];        // kept item: RoI * NPART + part
+    float ax[ITEMS][4];
+    int rng[ITEMS][4];   // its tap extent ymin, ymax, xmin, xmax
     int n;
 };
 
@@ -330,7 +340,8 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
     using SM = GatherSmem<TG, PH, PW, S>;
     constexpr int NR = SM::NR, NCOL = SM::NCOL, T = SM::T, NB = SM::NB, GB = SM::GB;
     constexpr int NBUF = SM::NBUF;
-    constexpr int YP = (PH * T + 63) / 64;   // ballot passes for the row weights
+    constexpr int RP = SM::RP, NPART = SM::NPART;
+    constexpr int YP = (RP * T + 63) / 64;   // ballot passes for the row weights
     constexpr int XP = (PW * T + 63) / 64;
     static_assert(NR + NCOL <= 64, "taps are computed by one wavefront");
     static_assert(PH <= 32 && PW <= 32, "bin masks are 32-bit");
@@ -361,13 +372,40 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
     const bool wide = (kstride * int64_t(sizeof(TG)) & 15) == 0 &&
                       (reinterpret_cast<uintptr_t>(h.gout) & 15u) == 0;
     auto fetch = [&](int j, uint32_t *gdst) {
-        const int k = uniform_i(sm.k[j]);   // one resource for the wave, no waterfall
+        const int item = uniform_i(sm.k[j]);   // one resource for the wave, no waterfall
         const char *src = static_cast<const char *>(h.gout) +
-                          (static_cast<int64_t>(x.cg) * 64 * NB + static_cast<int64_t>(k) * kstride) *
+                          (static_cast<int64_t>(x.cg) * 64 * NB + static_cast<int64_t>(item / NPART) * kstride) *
                               int64_t(sizeof(TG));
         const __amdgpu_buffer_rsrc_t rs = make_rsrc(src, static_cast<uint32_t>(nvalid) * uint32_t(sizeof(TG)));
         constexpr int NRUN = SM::NRUN;
-        if (wide) {
+        if constexpr (NPART > 1) {
+            // a part: every channel's rows from byte p0 on, 16 (or 4) bytes per lane, PITCH / 4
+            // (PITCH) pieces per channel of which the last are past the part and read zeros
+            const int p0 = (item % NPART) * RP * PW * 4;
+            const int len = min(RP * PW * 4, NB * 4 - p0);
+            if (wide) {
+                constexpr int PC = SM::PITCH / 4;
+                static_assert(PC == 29, "the quotient below");
+                for (int run = wave; run < PC; run += 4) {
+                    const int q = run * 64 + lane;
+                    const int ch = (q * 2260) >> 16;   // q / 29 for q < 64 * 29
+                    const int at = (q - ch * PC) * 16;
+                    auto *dst = (__attribute__((address_space(3))) void *)(gdst + 256 * run);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                        rs, dst, 16, at < len ? static_cast<uint32_t>(ch * NB * 4 + p0 + at) : kBufOOB, 0, 0, 0);
+                }
+            } else {
+                constexpr int PC = SM::PITCH;
+                for (int run = wave; run < PC; run += 4) {
+                    const int q = run * 64 + lane;
+                    const int ch = (q * 565) >> 16;    // q / 116 for q < 64 * 116
+                    const int at = (q - ch * PC) * 4;
+                    auto *dst = (__attribute__((address_space(3))) void *)(gdst + 64 * run);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                        rs, dst, 4, at < len ? static_cast<uint32_t>(ch * NB * 4 + p0 + at) : kBufOOB, 0, 0, 0);
+                }
+            }
+        } else if (wide) {
 #pragma unroll
             for (int m = 0; m < (NRUN + 3) / 4; ++m) {
                 const int run = wave + 4 * m;
@@ -421,6 +459,7 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
         const int ymin = sm.rng[j][0], ymax = sm.rng[j][1];
         const int xmin = sm.rng[j][2], xmax = sm.rng[j][3];
         if (!x.wave_on || ymax < R0 || ymin >= R0 + T || xmax < Q0 || xmin >= Q0 + T) return;
+        const int ph0 = NPART == 1 ? 0 : (uniform_i(sm.k[j]) % NPART) * RP;   // the part's first bin row
         // This quadrant's separable weights and which bin rows / columns reach it.
         // Ballot bit p * 64 + i marks a nonzero weight of lane u = p * 64 + i
         // (u = bin * 8 + row or column of the quadrant).
@@ -429,8 +468,8 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
         for (int p = 0; p < YP; ++p) {
             const int u = p * 64 + lane;
             bool hit = false;
-            if (u < PH * T) {
-                const int ph = u / T;
+            const int ph = ph0 + u / T;
+            if (u < RP * T && ph < PH) {
                 const int R = R0 + (u % T);
                 float w = 0.0f;
 #pragma unroll
@@ -473,7 +512,7 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
         if (pha < 0 || pwa < 0) return;
         wave_sync();
 
-        const typename SM::Elem *gl = gsrc + lane * NB + pwa;   // this lane's channel, stride NB
+        const typename SM::Elem *gl = gsrc + lane * SM::PITCH + pwa;   // this lane's channel
         const float *wxa = wx + pwa * T;
         gather_rows<TG, PW>(acc, gl, wxa, wy, yb, pha, phb, pwb - pwa + 1);
         // the weights are rewritten for the next RoI only after the next barrier
@@ -486,9 +525,9 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
         // RoIs whose tap extent misses the workgroup's region reach none of its pixels
         // and are dropped; the rest are compacted.
         if (wave == 0) {
-            bool keep = false;
-            int k = 0, ymin = INT32_MAX, ymax = -1, xmin = INT32_MAX, xmax = -1;
-            float ax_s = 0.0f, ax_b = 0.0f, ay_s = 0.0f, ay_b = 0.0f;
+            bool on = false;
+            int k = 0, xmin = INT32_MAX, xmax = -1;
+            Axis ax{}, ay{};
             if (lane < n) {
                 k = h.tile_rois[base + lane];
                 if (k >= 0 && k < h.K) {
@@ -496,45 +535,49 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
                     const float r0 = r[0], x1 = r[1], y1 = r[2], x2 = r[3], y2 = r[4];
                     const int lvl = h.roi_levels ? h.roi_levels[k] : 0;
                     if (lvl == l && roi_batch(r0, lv.N) == b) {
-                        const Axis ax = axis_setup(x1, x2, L.scale, h.aligned, PW, S);
-                        const Axis ay = axis_setup(y1, y2, L.scale, h.aligned, PH, S);
-                        ax_s = ax.start;
-                        ax_b = ax.bin;
-                        ay_s = ay.start;
-                        ay_b = ay.bin;
+                        ax = axis_setup(x1, x2, L.scale, h.aligned, PW, S);
+                        ay = axis_setup(y1, y2, L.scale, h.aligned, PH, S);
                         // Tap extent from the first and last sample of each axis (taps
                         // are monotone in the sample index); an end sample outside the
                         // map widens the extent to the map edge, so it is a superset.
-                        const Tap fy = axis_tap(ay, 0, 0, L.H);
-                        const Tap ly = axis_tap(ay, PH - 1, S - 1, L.H);
                         const Tap fx = axis_tap(ax, 0, 0, L.W);
                         const Tap lx = axis_tap(ax, PW - 1, S - 1, L.W);
-                        ymin = fy.lo >= 0 ? fy.lo : 0;
-                        ymax = ly.lo >= 0 ? ly.hi : L.H - 1;
                         xmin = fx.lo >= 0 ? fx.lo : 0;
                         xmax = lx.lo >= 0 ? lx.hi : L.W - 1;
-                        const bool yhit = ymax >= x.WR0 && ymin < x.WR1;
-                        const bool xhit = xmax >= x.WC0 && xmin < x.WC1;
-                        keep = yhit && xhit;
+                        on = xmax >= x.WC0 && xmin < x.WC1;
                     }
                 }
             }
-            const uint64_t km = __ballot(keep);
-            if (keep) {
-                const int pos = static_cast<int>(__builtin_amdgcn_mbcnt_hi(
-                    static_cast<uint32_t>(km >> 32),
-                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(km), 0u)));
-                sm.k[pos] = k;
-                sm.ax[pos][0] = ax_s;
-                sm.ax[pos][1] = ax_b;
-                sm.ax[pos][2] = ay_s;
-                sm.ax[pos][3] = ay_b;
-                sm.rng[pos][0] = ymin;
-                sm.rng[pos][1] = ymax;
-                sm.rng[pos][2] = xmin;
-                sm.rng[pos][3] = xmax;
+            int kept = 0;
+#pragma unroll
+            for (int part = 0; part < NPART; ++part) {
+                bool keep = false;
+                int ymin = 0, ymax = -1;
+                if (on) {
+                    const Tap fy = axis_tap(ay, part * RP, 0, L.H);
+                    const Tap ly = axis_tap(ay, min(PH, part * RP + RP) - 1, S - 1, L.H);
+                    ymin = fy.lo >= 0 ? fy.lo : 0;
+                    ymax = ly.lo >= 0 ? ly.hi : L.H - 1;
+                    keep = ymax >= x.WR0 && ymin < x.WR1;
+                }
+                const uint64_t km = __ballot(keep);
+                if (keep) {
+                    const int pos = kept + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+                        static_cast<uint32_t>(km >> 32),
+                        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(km), 0u)));
+                    sm.k[pos] = k * NPART + part;
+                    sm.ax[pos][0] = ax.start;
+                    sm.ax[pos][1] = ax.bin;
+                    sm.ax[pos][2] = ay.start;
+                    sm.ax[pos][3] = ay.bin;
+                    sm.rng[pos][0] = ymin;
+                    sm.rng[pos][1] = ymax;
+                    sm.rng[pos][2] = xmin;
+                    sm.rng[pos][3] = xmax;
+                }
+                kept += __builtin_popcountll(km);
             }
-            if (lane == 0) sm.n = __builtin_popcountll(km);
+            if (lane == 0) sm.n = kept;
         }
         __syncthreads();
         const int nk = sm.n;
@@ -577,8 +620,9 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
 }
 
 
+// Four workgroups per CU: every instance fits 40 KiB of LDS and, held to it, 128 registers.
 template <typename TG, int PH, int PW, int S>
-__global__ __launch_bounds__(256) void bwd_gather_kernel(GatherArgs a) {
+__global__ __launch_bounds__(256, 4) void bwd_gather_kernel(GatherArgs a) {
     __shared__ GatherSmem<TG, PH, PW, S> sm;
     __shared__ GatherBlock<TG, PH, PW, S> blk0;
     constexpr bool two = GatherSmem<TG, PH, PW, S>::NBUF == 2;
@@ -603,7 +647,7 @@ __global__ __launch_bounds__(256) void bwd_gather_kernel(GatherArgs a) {
 // same accumulators, and writes every gradient element once.  Tiles follow head 0's
 // order.
 template <typename TG, int PH0, int PW0, int PH1, int PW1>
-__global__ __launch_bounds__(256) void bwd_gather2_kernel(GatherArgs a) {
+__global__ __launch_bounds__(256, 4) void bwd_gather2_kernel(GatherArgs a) {
     using SM0 = GatherSmem<TG, PH0, PW0, 2>;
     using SM1 = GatherSmem<TG, PH1, PW1, 2>;
     union Smem {
