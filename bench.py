@@ -75,7 +75,8 @@ def parse():
 
 
 ALL_SOURCES = ("common.hpp", "internal.hpp", "gather.hpp", "plan.hip", "fwd.hip", "bwd.hip",
-               "pool.hip", "deform.hip", "nms.hip", "select.hip", "api.hip")
+               "adaptive.hip", "pool.hip", "deform.hip", "nms.hpp", "nms.hip", "select.hip",
+               "api.hip")
 # the sources a kernel's code comes from (its device code and the shared headers)
 KERNEL_SOURCES = {"fwd": ("common.hpp", "internal.hpp", "fwd.hip"),
                   "bwd_gather": ("common.hpp", "internal.hpp", "gather.hpp", "bwd.hip"),
