@@ -42,9 +42,13 @@ __device__ __forceinline__ float any_position(const Axis &a, int p, int i, int s
 }
 
 // Summed weight the samples of bin p put on pixel X of the axis, and whether any of them
-// taps it (also with weight zero).  pos holds the bin's positions.  Only samples within a
-// pixel of X can tap it, and the raw positions are evenly spaced, so the loop runs over
-// their index range, widened by one for rounding; a box without extent takes all samples.
+// taps it (also with weight zero).  pos holds the bin's positions.  Only samples whose position
+// before the clamp is within a pixel of X can tap it -- and, for X <= 1, all those clamped up
+// to 0 -- and these positions are evenly spaced, so the loop runs over their index range.  It
+// is widened by one, and by what the rounding of a position and of `rel` comes to in units of
+// the spacing: at most 8 units of 2^-24 of the coordinate (samples closer than that round to
+// one position) and of the box, whose part the widening by one covers.  A box without extent
+// takes all samples.
 __device__ __forceinline__ float any_weight(const float *pos, const Axis &a, int p, int X, int size,
                                             bool &hit) {
     const float g = static_cast<float>(a.grid);
@@ -52,9 +56,10 @@ __device__ __forceinline__ float any_weight(const float *pos, const Axis &a, int
     if (a.bin > 0.0f) {
         const float inv = g * __builtin_amdgcn_rcpf(a.bin);
         const float rel = (static_cast<float>(X) - a.start) - static_cast<float>(p) * a.bin;
-        const float lo = (rel - 1.0f) * inv - 1.5f;   // floor - 1 of the first index
-        const float hi = (rel + 1.0f) * inv + 0.5f;   // ceil + 1 of the last
-        if (lo > 0.0f) i0 = static_cast<int>(fminf(lo, g));
+        const float slack = (static_cast<float>(X) + 2.0f) * inv * 0x1p-21f;
+        const float lo = (rel - 1.0f) * inv - (1.5f + slack);   // floor - 1 of the first index
+        const float hi = (rel + 1.0f) * inv + (0.5f + slack);   // ceil + 1 of the last
+        if (X > 1 && lo > 0.0f) i0 = static_cast<int>(fminf(lo, g));
         if (hi < g - 1.0f) i1 = static_cast<int>(fmaxf(hi, -1.0f));
     }
     float w = 0.0f;

@@ -110,6 +110,20 @@ def test_many_samples():
     _run("many", rois, 7, 0, shapes=[(1, 5, 200, 500)], scales=[1.0])
 
 
+@pytest.mark.parametrize("S", [3, 4, 64])
+def test_samples_closer_than_a_unit(S):
+    # boxes a few units in the last place wide: all samples of a bin round to one position, which
+    # at the map's edges is cut or clamped as a whole (the window over the samples is compared
+    # with the sum over all of them on the CPU, test_any_window_cpu.py)
+    rois = []
+    for x, y in ((362, 40), (361, 102), (-2, 3), (-1.9, -2), (30, 30)):
+        x2, y2 = np.float32(x), np.float32(y)
+        for _ in range(3):
+            x2, y2 = np.nextafter(x2, np.float32(np.inf)), np.nextafter(y2, np.float32(np.inf))
+            rois += [[0, x, y, x2, y2], [1, x, 20, x2, 50], [0, 100, y, 160, y2]]
+    _run("tiny", np.array(rois, np.float32), 7, S)
+
+
 def test_levels_not_the_plans():
     # a caller's own levels: the tile lists hold the RoIs on the plan's levels only
     _run("stray", _mixed_rois(), 7, 0, levels=lambda lv: (lv + (np.arange(lv.size) % 3 == 0)) % 3)
