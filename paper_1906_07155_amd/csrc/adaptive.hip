@@ -41,18 +41,16 @@ __device__ __forceinline__ float any_position(const Axis &a, int p, int i, int s
     return static_cast<int>(v) >= size - 1 ? static_cast<float>(size - 1) : v;
 }
 
-// Summed weight the samples of bin p put on pixel X of the axis, and whether any of them
-// taps it (also with weight zero).  pos holds the bin's positions.  Only samples whose position
-// before the clamp is within a pixel of X can tap it -- and, for X <= 1, all those clamped up
-// to 0 -- and these positions are evenly spaced, so the loop runs over their index range.  It
-// is widened by one, and by what the rounding of a position and of `rel` comes to in units of
-// the spacing: at most 8 units of 2^-24 of the coordinate (samples closer than that round to
-// one position) and of the box, whose part the widening by one covers.  A box without extent
-// takes all samples.
-__device__ __forceinline__ float any_weight(const float *pos, const Axis &a, int p, int X, int size,
-                                            bool &hit) {
+// The samples i0..i1 of bin p that can tap pixel X of the axis: only those whose position
+// before the clamp is within a pixel of X and, for X <= 1, all those clamped up to 0.  The
+// positions are evenly spaced, so they are an index range, widened by one and by what the
+// rounding of a position and of `rel` comes to in units of the spacing: at most 8 units of
+// 2^-24 of the coordinate (samples closer than that round to one position) and of the box,
+// whose part the widening by one covers.  A box without extent takes all samples.
+__device__ __forceinline__ void any_window(const Axis &a, int p, int X, int &i0, int &i1) {
     const float g = static_cast<float>(a.grid);
-    int i0 = 0, i1 = a.grid - 1;
+    i0 = 0;
+    i1 = a.grid - 1;
     if (a.bin > 0.0f) {
         const float inv = g * __builtin_amdgcn_rcpf(a.bin);
         const float rel = (static_cast<float>(X) - a.start) - static_cast<float>(p) * a.bin;
@@ -62,6 +60,14 @@ __device__ __forceinline__ float any_weight(const float *pos, const Axis &a, int
         if (X > 1 && lo > 0.0f) i0 = static_cast<int>(fminf(lo, g));
         if (hi < g - 1.0f) i1 = static_cast<int>(fmaxf(hi, -1.0f));
     }
+}
+
+// Summed weight the samples of bin p put on pixel X, and whether any of them taps it (also
+// with weight zero).  pos holds the bin's positions.
+__device__ __forceinline__ float any_weight(const float *pos, const Axis &a, int p, int X, int size,
+                                            bool &hit) {
+    int i0, i1;
+    any_window(a, p, X, i0, i1);
     float w = 0.0f;
     hit = false;
 #pragma unroll 1
@@ -502,8 +508,9 @@ hipError_t launch_fwd_any(const FwdArgs &a, int feat_dtype, int out_dtype, hipSt
 // sample positions, which the workgroup puts in LDS while the RoI's gradient block is
 // copied.  The tile lists hold every RoI whose samples can tap the tile, whatever their
 // number.  A non-finite sum in a tile (a NaN or infinity upstream, or an overflow) makes
-// the workgroup walk its list once more, adding every product only where a sample taps
-// the pixel, as the scatter does.
+// the workgroup walk its list twice more: once for the finite gradients, product by product,
+// and once for the pixels that the others reach and what the definition's products make of
+// them, which is added to the sums in memory.
 template <typename TG, int P>
 struct AnyGatherSmem {
     static constexpr int T = 8;
@@ -522,32 +529,56 @@ struct AnyGatherSmem {
     int n;
 };
 
-// One bin's products added to the gradient in memory where its samples tap the pixel: bit r
-// of rb (q of qb) marks a tapped row (column) of the quadrant at byte `base` of the image.
-// The workgroup owns the tile and the lane its channel, so plain adds do.
-__device__ __forceinline__ void gather_exact_bin(__amdgpu_buffer_rsrc_t dst, uint32_t vo,
-                                                 uint32_t base, uint32_t sh4, uint32_t sw4, float g,
-                                                 const float *wy, const float *wx, uint32_t rb,
-                                                 uint32_t qb) {
+// The smallest and largest weight a sample of bin p puts on pixel X; false if none taps it.
+// A sample on the last pixel taps it twice, the second time with weight zero, as axis_tap has it.
+__device__ __forceinline__ bool any_extremes(const float *pos, const Axis &a, int p, int X, int size,
+                                             float &least, float &most) {
+    int i0, i1;
+    any_window(a, p, X, i0, i1);
+    least = 2.0f;
+    most = -1.0f;
 #pragma unroll 1
-    for (uint32_t rm = rb; rm; rm &= rm - 1) {
-        const int r = __builtin_ctz(rm);
-        const float gy = wy[r] * g;
-#pragma unroll 1
-        for (uint32_t qm = qb; qm; qm &= qm - 1) {
-            const int q = __builtin_ctz(qm);
-            const uint32_t o = base + static_cast<uint32_t>(r) * sh4 + static_cast<uint32_t>(q) * sw4;
-            const float old = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dst, vo, o, 0));
-            const float v = fmaf(wx[q], gy, old);
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), dst, vo, o, 0);
-            __builtin_amdgcn_s_waitcnt(0x0F70);   // before the next bin reads the pixel
+    for (int i = i0; i <= i1; ++i) {
+        const float v = pos[i];
+        if (!(v >= 0.0f)) continue;
+        const int l = static_cast<int>(v);
+        const float f = v - static_cast<float>(l);
+        if (l == X) {
+            least = fminf(least, 1.0f - f);
+            most = fmaxf(most, 1.0f - f);
+        }
+        if (min(l + 1, size - 1) == X) {
+            least = fminf(least, f);
+            most = fmaxf(most, f);
         }
     }
+    return most >= 0.0f;
 }
 
-// Walks the tile's RoIs; add(gl, wy, wx, yb, xb, pha, phb, pwa, pwb) takes one RoI's part of
-// the wave's quadrant: the lane's gradient block gl, the weights (wy with 1 / count), the
-// tapped (bin, pixel) pairs as ballots, and the runs of bins that reach the quadrant.
+// What a bin's non-finite gradients do to the quadrant, as bits r * 8 + q of its pixels: an
+// infinity times a positive weight is infinite, times a zero weight NaN, and a NaN is NaN on
+// every tapped pixel.  A weight is the product of a row's and a column's; it is monotone in
+// both, so the extremes of the two axes tell whether some sample's is zero and whether some
+// sample's is not.
+struct GatherMarks {
+    uint64_t nan, up, down;   // of the lane's channel
+};
+
+// One RoI's part of a wave's quadrant: its sample positions, the lane's gradient block, the
+// weights (wy with 1 / count), the tapped (row bin, row) pairs as ballots, and the runs of bins
+// that reach the quadrant.
+template <int NP>
+struct AnyItem {
+    Axis ay, ax;
+    const float *ypos, *xpos;
+    const uint32_t *gl;
+    const float *wy, *wx;
+    uint64_t yb[NP];
+    int pha, phb, pwa, pwb;
+    float inv_count;
+};
+
+// Walks the tile's RoIs and hands each one's part of the wave's quadrant to add.
 template <typename TG, int P, typename Add>
 __device__ __forceinline__ void any_phase(const GatherHead &h, const LevelTable &lv, int S, int t,
                                           const GatherTile &x, AnyGatherSmem<TG, P> &sm,
@@ -612,25 +643,36 @@ __device__ __forceinline__ void any_phase(const GatherHead &h, const LevelTable 
         if (!x.wave_on || ymax < R0 || ymin >= R0 + T || xmax < Q0 || xmin >= Q0 + T) return;
         const Axis ay = sm.ay[j], ax = sm.ax[j];
         const float inv_count = 1.0f / static_cast<float>(max(ay.grid * ax.grid, 1));
-        uint64_t yb[NP], xb[NP];
+        uint64_t xb[NP];
+        AnyItem<NP> it;
+        it.ay = ay;
+        it.ax = ax;
+        it.ypos = pos;
+        it.xpos = pos + kAnyGrid * P;
+        it.inv_count = inv_count;
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             const int u = p * 64 + lane;
             bool hy = false, hx = false;
             if (u < P * T) {
                 const int bin = u / T;
-                const float w = any_weight(pos + bin * ay.grid, ay, bin, R0 + (u % T), L.H, hy);
+                const float w = any_weight(it.ypos + bin * ay.grid, ay, bin, R0 + (u % T), L.H, hy);
                 wy[u] = w * inv_count;
-                wx[u] = any_weight(pos + kAnyGrid * P + bin * ax.grid, ax, bin, Q0 + (u % T), L.W, hx);
+                wx[u] = any_weight(it.xpos + bin * ax.grid, ax, bin, Q0 + (u % T), L.W, hx);
             }
-            yb[p] = __ballot(hy);
+            it.yb[p] = __ballot(hy);
             xb[p] = __ballot(hx);
         }
-        const int pha = first_set(yb) / T, phb = last_set(yb) / T;
-        const int pwa = first_set(xb) / T, pwb = last_set(xb) / T;
-        if (first_set(yb) < 0 || first_set(xb) < 0) return;
+        if (first_set(it.yb) < 0 || first_set(xb) < 0) return;
+        it.pha = first_set(it.yb) / T;
+        it.phb = last_set(it.yb) / T;
+        it.pwa = first_set(xb) / T;
+        it.pwb = last_set(xb) / T;
+        it.gl = gsrc + lane * NB;
+        it.wy = wy;
+        it.wx = wx;
         wave_sync();
-        add(gsrc + lane * NB, wy, wx, yb, xb, pha, phb, pwa, pwb);
+        add(it);
     };
 
     for (int base = s0; base < s1; base += 64) {
@@ -739,12 +781,10 @@ __global__ __launch_bounds__(256, P == 7 ? 4 : 2) void bwd_gather_any_kernel(Gat
     for (int r = 0; r < 8; ++r)
 #pragma unroll
         for (int q = 0; q < 8; ++q) acc[r][q] = 0.0f;
-    any_phase<TG, P>(a.head[0], a.lv, a.S, t, x, sm, blk0, slot1,
-                     [&](const uint32_t *gl, const float *wy, const float *wx, const uint64_t (&yb)[NP],
-                         const uint64_t (&)[NP], int pha, int phb, int pwa, int pwb) {
-                         gather_rows<TG, P>(acc, gl + pwa, wx + pwa * 8, wy, yb, pha, phb,
-                                            pwb - pwa + 1);
-                     });
+    any_phase<TG, P>(a.head[0], a.lv, a.S, t, x, sm, blk0, slot1, [&](const AnyItem<NP> &it) {
+        gather_rows<TG, P>(acc, it.gl + it.pwa, it.wx + it.pwa * 8, it.wy, it.yb, it.pha, it.phb,
+                           it.pwb - it.pwa + 1);
+    });
     bool bad = false;
 #pragma unroll
     for (int r = 0; r < 8; ++r)
@@ -752,46 +792,77 @@ __global__ __launch_bounds__(256, P == 7 ? 4 : 2) void bwd_gather_any_kernel(Gat
         for (int q = 0; q < 8; ++q) bad = bad || !__builtin_isfinite(acc[r][q]);
     static_assert(SM::GBP >= 4 * 512, "store scratch in the first slot");
     // also the barrier after which the staging slots are free
-    if (!__syncthreads_or(bad && x.wave_on)) {
-        gather_store(x, a.zero_init, acc, reinterpret_cast<float *>(blk0) + (threadIdx.x >> 6) * 512);
-        return;
-    }
-    // The exact walk: the quadrant cleared in memory, then every product added there (the
-    // accumulators are free, so this rare path costs the other no registers).
+    const bool exact = __syncthreads_or(bad && x.wave_on);
     const int lane = threadIdx.x & 63;
-    const char *img = static_cast<const char *>(x.L.data) + static_cast<int64_t>(x.b) * x.L.sn * 4;
-    const __amdgpu_buffer_rsrc_t dst = make_rsrc(img, x.L.img_bytes);
-    const uint32_t vo = lane < x.nch ? static_cast<uint32_t>(x.cg * 64 + lane) *
-                                           static_cast<uint32_t>(x.L.sc) * 4u
-                                     : kBufOOB;
-    const uint32_t sh4 = static_cast<uint32_t>(x.L.sh) * 4u, sw4 = static_cast<uint32_t>(x.L.sw) * 4u;
-    const uint32_t base = static_cast<uint32_t>(x.R0) * sh4 + static_cast<uint32_t>(x.Q0) * sw4;
-    if (a.zero_init && x.wave_on) {
-        const int nr = min(8, x.L.H - x.R0), nq = min(8, x.L.W - x.Q0);
+    if (exact) {
+        // A NaN or infinity upstream (or an overflow on the way): the list once more, bin by
+        // bin and product by product, with the finite gradients only.
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc[r][q] = 0.0f;
+        any_phase<TG, P>(a.head[0], a.lv, a.S, t, x, sm, blk0, slot1, [&](const AnyItem<NP> &it) {
 #pragma unroll 1
-        for (int r = 0; r < nr; ++r)
+            for (int ph = it.pha; ph <= it.phb; ++ph) {
+                const uint32_t rb =
+                    static_cast<uint32_t>(it.yb[NP == 1 ? 0 : ph >> 3] >> ((ph & 7) * 8)) & 0xffu;
 #pragma unroll 1
-            for (int q = 0; q < nq; ++q)
-                __builtin_amdgcn_raw_buffer_store_b32(0u, dst, vo, base + static_cast<uint32_t>(r) * sh4 +
-                                                      static_cast<uint32_t>(q) * sw4, 0);
-        __builtin_amdgcn_s_waitcnt(0x0F70);
+                for (int pw = it.pwa; pw <= it.pwb; ++pw) {
+                    // lane = pixel of the quadrant (zero where no sample taps it)
+                    const float w = it.wy[ph * 8 + (lane >> 3)] * it.wx[pw * 8 + (lane & 7)];
+                    float g = raw_to_f32<TG>(it.gl[ph * P + pw]);
+                    g = __builtin_isfinite(g) ? g : 0.0f;
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) {
+                        if (((rb >> r) & 1u) == 0) continue;
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+                            acc[r][q] = fmaf(__int_as_float(__builtin_amdgcn_readlane(
+                                                 __float_as_int(w), 8 * r + q)), g, acc[r][q]);
+                    }
+                }
+            }
+        });
+        __syncthreads();   // the staging slots are free again
     }
-    any_phase<TG, P>(a.head[0], a.lv, a.S, t, x, sm, blk0, slot1,
-                     [&](const uint32_t *gl, const float *wy, const float *wx, const uint64_t (&yb)[NP],
-                         const uint64_t (&xb)[NP], int pha, int phb, int pwa, int pwb) {
+    gather_store(x, a.zero_init, acc, reinterpret_cast<float *>(blk0) + (threadIdx.x >> 6) * 512);
+    if (!exact) return;
+    // The non-finite gradients: which pixels they reach, then those pixels' values.
+    GatherMarks m{0, 0, 0};
+    any_phase<TG, P>(a.head[0], a.lv, a.S, t, x, sm, blk0, slot1, [&](const AnyItem<NP> &it) {
+        const int Y = x.R0 + (lane >> 3), X = x.Q0 + (lane & 7);
 #pragma unroll 1
-                         for (int ph = pha; ph <= phb; ++ph) {
-                             const uint32_t rb =
-                                 static_cast<uint32_t>(yb[NP == 1 ? 0 : ph >> 3] >> ((ph & 7) * 8)) & 0xffu;
+        for (int ph = it.pha; ph <= it.phb; ++ph) {
+            float ly, my;
+            const bool hy = any_extremes(it.ypos + ph * it.ay.grid, it.ay, ph, Y, x.L.H, ly, my);
 #pragma unroll 1
-                             for (int pw = pwa; pw <= pwb; ++pw) {
-                                 const uint32_t qb = static_cast<uint32_t>(
-                                     xb[NP == 1 ? 0 : pw >> 3] >> ((pw & 7) * 8)) & 0xffu;
-                                 gather_exact_bin(dst, vo, base, sh4, sw4, raw_to_f32<TG>(gl[ph * P + pw]),
-                                                  wy + ph * 8, wx + pw * 8, rb, qb);
-                             }
-                         }
-                     });
+            for (int pw = it.pwa; pw <= it.pwb; ++pw) {
+                const float g = raw_to_f32<TG>(it.gl[ph * P + pw]);
+                if (__ballot(!__builtin_isfinite(g)) == 0) continue;
+                float lx, mx;
+                const bool hx = any_extremes(it.xpos + pw * it.ax.grid, it.ax, pw, X, x.L.W, lx, mx);
+                const uint64_t hit = __ballot(hy && hx);
+                const uint64_t zero = __ballot(hy && hx && ly * lx == 0.0f);
+                const uint64_t some = __ballot(hy && hx && my * mx != 0.0f);
+                const float inf = __builtin_inff();
+                m.nan |= g != g ? hit : fabsf(g) == inf ? zero : 0;
+                m.up |= g == inf ? some : 0;
+                m.down |= g == -inf ? some : 0;
+            }
+        }
+    });
+    if (!x.wave_on || lane >= x.nch) return;
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // the wave's stores above are done
+    float *const base = static_cast<float *>(const_cast<void *>(x.L.data)) + x.b * x.L.sn +
+                        (x.cg * 64 + lane) * x.L.sc;
+    for (uint64_t todo = m.nan | m.up | m.down; todo; todo &= todo - 1) {
+        const int i = __builtin_ctzll(todo);
+        float *const px = base + (x.R0 + (i >> 3)) * x.L.sh + (x.Q0 + (i & 7)) * x.L.sw;
+        const bool up = (m.up >> i) & 1, down = (m.down >> i) & 1;
+        const float v = ((m.nan >> i) & 1) || (up && down) ? __builtin_nanf("")
+                                                           : up ? __builtin_inff() : -__builtin_inff();
+        *px += v;
+    }
 }
 
 // The RoIs whose level differs from the one the plan gave them (a caller may pass levels of

@@ -145,28 +145,63 @@ def test_non_finite_feature():
         check_fwd(np.where(ok, out, 0), np.where(ok, ref, 0), False, "non-finite feature")
 
 
-@pytest.mark.parametrize("zero_init", [True, False])
-@pytest.mark.parametrize("layout", ["cl", "nchw"])
-def test_non_finite_gradient(layout, zero_init):
-    # as the scatter: exactly the tapped pixels take the value
-    rois = _mixed_rois()
+def _as_the_scatter(rois, g, P, S, aligned, layout, zero_init):
+    """RE_BWD_AUTO's pyramid has the scatter's infinities and NaNs, element by element."""
     rng, feats, dev, r, lv, ws, lv_np = _setup(rois, SHAPES, SCALES, "f32", layout)
-    g = rng.standard_normal((rois.shape[0], 70, 7, 7), dtype=np.float32)
-    g[4, 2, 3, 3] = np.inf
-    g[20, 69, 0, 6] = np.nan
-    gd = torch.from_numpy(g).cuda()
+    gd = g.cuda()
     res = []
     for algo in ("auto", "scatter"):
         grads = [torch.full(s, 7.0, dtype=torch.float32, device="cuda") for s in SHAPES]
         if layout == "cl":
             grads = [x.contiguous(memory_format=torch.channels_last) for x in grads]
-        rex.roi_align_bwd(gd, r, lv, (7, 7), 0, True, grads, SCALES, zero_init=zero_init,
+        rex.roi_align_bwd(gd, r, lv, (P, P), S, aligned, grads, SCALES, zero_init=zero_init,
                           workspace=ws, algorithm=algo)
         res.append([from_device(x) for x in grads])
     for a, s in zip(*res):
-        assert np.array_equal(np.isfinite(a), np.isfinite(s))
         assert np.array_equal(np.isnan(a), np.isnan(s))
+        assert np.array_equal(np.isposinf(a), np.isposinf(s))
+        assert np.array_equal(np.isneginf(a), np.isneginf(s))
         ok = np.isfinite(s)
         # the same products in two orders: 1e-4 of the sums' scale, as the gather against
         # the oracle
         assert np.all(np.abs(a[ok] - s[ok]) <= 1e-4 * np.maximum(np.abs(s[ok]), 1.0))
+    return res[1]
+
+
+@pytest.mark.parametrize("zero_init", [True, False])
+@pytest.mark.parametrize("layout", ["cl", "nchw"])
+def test_non_finite_gradient(layout, zero_init):
+    # as the scatter: exactly the tapped pixels take the value
+    rois = _mixed_rois()
+    g = torch.from_numpy(np.random.default_rng(1).standard_normal((rois.shape[0], 70, 7, 7),
+                                                                  dtype=np.float32))
+    g[4, 2, 3, 3] = np.inf
+    g[20, 69, 0, 6] = np.nan
+    _as_the_scatter(rois, g, 7, 0, True, layout, zero_init)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("P,S,zero_init", [(7, 0, True), (7, 1, True), (7, 3, False), (7, 4, True),
+                                           (14, 0, False), (14, 4, True)])
+def test_non_finite_gradient_on_integer_samples(P, S, zero_init, dt):
+    # A sample on a pixel taps the next one with weight zero, and zero times an infinity is NaN,
+    # whatever other samples of the bin give that pixel; so does a sample on the last pixel (or
+    # clamped to it) with that pixel, and one clamped to pixel 0 with pixel 1.  Boxes on level 0
+    # (scale 1/4, 25 x 90 pixels) whose bins are 1, 2 or 4 pixels wide from a quarter of a pixel on.
+    rois = []
+    for bin_ in (1.0, 2.0, 0.25):
+        for at in (3.0, 3.5, 3.25, -1.0, -0.5, 88.0 - 7 * bin_, 89.5 - 7 * bin_, 91.0 - 7 * bin_):
+            for top in (2.0, 2.5, -0.5, 20.5 - 7 * bin_):
+                x1, y1 = (at + 0.5) * 4, (top + 0.5) * 4
+                rois.append([len(rois) % 2, x1, y1, x1 + P * bin_ * 4, y1 + P * bin_ * 4])
+    rois = np.array(rois, np.float32)
+    rng = np.random.default_rng(P + S)
+    g = rng.standard_normal((len(rois), 70, P, P), dtype=np.float32)
+    for value in (np.inf, -np.inf, np.nan, 2e38):
+        for _ in range(60):
+            g[rng.integers(len(rois)), rng.integers(70), rng.integers(P), rng.integers(P)] = value
+    g = torch.from_numpy(g)
+    if dt == "bf16":
+        g = g.to(torch.bfloat16)
+    s = _as_the_scatter(rois, g, P, S, True, "cl", zero_init)
+    assert np.isnan(s[0]).any() and np.isposinf(s[0]).any() and np.isneginf(s[0]).any()
