@@ -237,7 +237,11 @@ re_status_t roi_extract_zero_grad(const re_level_t *grad_levels, int32_t num_lev
  *           With a sampling ratio other than 2 on the 7x7 and 14x14 grids,
  *           RE_BWD_AUTO sums per tile as well when `plan` is given (RE_BWD_GATHER
  *           stays limited to 2): the result is the scatter's, also for RoIs whose
- *           roi_levels differ from the plan's and for non-finite values;
+ *           roi_levels differ from the plan's and for non-finite values.
+ *           Calls that add into one pyramid (zero_init == 0) may overlap on several
+ *           streams in the forms that add with atomics: the scatter, and AUTO's at
+ *           ratios other than 2.  The gather at ratio 2 loads, adds and stores every
+ *           element; such calls must be serialised;
  *   other arguments as roi_align_fwd. */
 re_status_t roi_align_bwd(const void *grad_out, int32_t grad_out_dtype,
                           const float *rois, int64_t num_rois, const int32_t *roi_levels,

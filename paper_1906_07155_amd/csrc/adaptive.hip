@@ -763,6 +763,46 @@ __device__ __forceinline__ void any_phase(const GatherHead &h, const LevelTable 
     }
 }
 
+// Accumulation: the quadrant's sums added with atomics, pixels no sample taps left alone, so
+// calls that add into one pyramid may overlap on two streams, as scatters may, and a call's
+// cost follows its RoIs and not the pyramid (against loading and storing every pixel: 8 RoIs on
+// four levels 36 -> 20 us, 512 RoIs 85 -> 98 us).  Channels in separate planes: a row of the
+// quadrant is turned around in the wave's LDS, so that an instruction adds to 8 runs of 8
+// adjacent pixels and not to 64 planes (512 RoIs: 1125 -> 213 us).
+constexpr int kAddPitch = 65;   // floats per pixel column in the scratch
+__device__ __forceinline__ void gather_add(const GatherTile &x, const float (&acc)[8][8], float *scratch) {
+    if (!x.wave_on) return;
+    const int lane = threadIdx.x & 63;
+    const LevelArg &L = x.L;
+    float *const base = static_cast<float *>(const_cast<void *>(L.data)) + x.b * L.sn +
+                        static_cast<int64_t>(x.cg * 64) * L.sc + x.R0 * L.sh + x.Q0 * L.sw;
+    const bool planes = L.sc != 1 && L.sw == 1;
+    const bool lane_on = lane < x.nch;
+    float *const mine = base + (lane_on ? lane : 0) * L.sc;
+    const int q8 = lane & 7, c8 = lane >> 3;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        if (x.R0 + r >= L.H) break;
+        if (planes) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) scratch[q * kAddPitch + lane] = acc[r][q];
+            wave_sync();
+#pragma unroll
+            for (int h = 0; h < 8; ++h) {
+                const int c = 8 * h + c8;
+                const float v = scratch[q8 * kAddPitch + c];
+                if (c < x.nch && x.Q0 + q8 < L.W && v != 0.0f) unsafeAtomicAdd(base + c * L.sc + r * L.sh + q8, v);
+            }
+            wave_sync();   // the row's values are read before the next row overwrites them
+        } else {
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (x.Q0 + q < L.W && lane_on && acc[r][q] != 0.0f)
+                    unsafeAtomicAdd(mine + r * L.sh + q * L.sw, acc[r][q]);
+        }
+    }
+}
+
 // 7x7: held to 128 registers (137 without, three waves per SIMD: 70 us against 58 us on the
 // batch above); 14x14: its 50 KiB block allows two workgroups per CU anyway.
 template <typename TG, int P>
@@ -790,7 +830,7 @@ __global__ __launch_bounds__(256, P == 7 ? 4 : 2) void bwd_gather_any_kernel(Gat
     for (int r = 0; r < 8; ++r)
 #pragma unroll
         for (int q = 0; q < 8; ++q) bad = bad || !__builtin_isfinite(acc[r][q]);
-    static_assert(SM::GBP >= 4 * 512, "store scratch in the first slot");
+    static_assert(SM::GBP >= 4 * 8 * kAddPitch, "store scratch in the first slot");
     // also the barrier after which the staging slots are free
     const bool exact = __syncthreads_or(bad && x.wave_on);
     const int lane = threadIdx.x & 63;
@@ -825,7 +865,9 @@ __global__ __launch_bounds__(256, P == 7 ? 4 : 2) void bwd_gather_any_kernel(Gat
         });
         __syncthreads();   // the staging slots are free again
     }
-    gather_store(x, a.zero_init, acc, reinterpret_cast<float *>(blk0) + (threadIdx.x >> 6) * 512);
+    float *const scratch = reinterpret_cast<float *>(blk0) + (threadIdx.x >> 6) * (8 * kAddPitch);
+    if (a.zero_init) gather_store(x, 1, acc, scratch);
+    else gather_add(x, acc, scratch);
     if (!exact) return;
     // The non-finite gradients: which pixels they reach, then those pixels' values.
     GatherMarks m{0, 0, 0};
@@ -861,7 +903,8 @@ __global__ __launch_bounds__(256, P == 7 ? 4 : 2) void bwd_gather_any_kernel(Gat
         const bool up = (m.up >> i) & 1, down = (m.down >> i) & 1;
         const float v = ((m.nan >> i) & 1) || (up && down) ? __builtin_nanf("")
                                                            : up ? __builtin_inff() : -__builtin_inff();
-        *px += v;
+        if (a.zero_init) *px += v;
+        else unsafeAtomicAdd(px, v);
     }
 }
 

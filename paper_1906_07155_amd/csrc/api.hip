@@ -633,32 +633,45 @@ bool head_gather_ok(const BwdHead &h, const LevelTable &t, const TileLayout &tl)
            gather_available(h.out_h, h.out_w, h.S);
 }
 
-// No two elements of a level share an address (strides grow past the extent of the smaller
-// ones): only then is writing every element once the same as adding to it.
+// No two elements of the pyramid share an address (within a level, strides grow past the
+// extent of the smaller ones; the levels' spans do not meet): only then is writing every
+// element once the same as adding to it.
 bool levels_distinct(const LevelTable &t) {
+    double span[kMaxLevels];   // elements from a level's first to its last
     for (int l = 0; l < t.num; ++l) {
         const int64_t ext[4] = {t.N, t.C, t.l[l].H, t.l[l].W};
         const int64_t str[4] = {t.l[l].sn, t.l[l].sc, t.l[l].sh, t.l[l].sw};
         bool used[4] = {ext[0] == 1, ext[1] == 1, ext[2] == 1, ext[3] == 1};
-        double span = 1.0;   // elements covered by the dimensions taken so far
+        span[l] = 1.0;
         for (;;) {
             int d = -1;
             for (int i = 0; i < 4; ++i)
                 if (!used[i] && (d < 0 || str[i] < str[d])) d = i;
             if (d < 0) break;
-            if (static_cast<double>(str[d]) < span) return false;
-            span += static_cast<double>(ext[d] - 1) * static_cast<double>(str[d]);
+            if (static_cast<double>(str[d]) < span[l]) return false;
+            span[l] += static_cast<double>(ext[d] - 1) * static_cast<double>(str[d]);
             used[d] = true;
+        }
+        const double a0 = static_cast<double>(reinterpret_cast<uintptr_t>(t.l[l].data));
+        for (int k = 0; k < l; ++k) {
+            const double b0 = static_cast<double>(reinterpret_cast<uintptr_t>(t.l[k].data));
+            if (a0 < b0 + 4.0 * span[k] && b0 < a0 + 4.0 * span[l]) return false;
         }
     }
     return true;
 }
 
 // The tile gather for sampling ratios other than 2 (RE_BWD_AUTO only): a fixed grid, a plan
-// with tile lists, levels the gather can address, and a grid of one dispatch.
-bool head_gather_any_ok(const BwdHead &h, const LevelTable &t, const TileLayout &tl) {
+// with tile lists, levels the gather can address, and a grid of one dispatch.  With zero_init
+// it stores (the levels must be distinct), without it adds with atomics, as the scatter does.
+bool head_gather_any_ok(const BwdHead &h, const LevelTable &t, const TileLayout &tl, int32_t zero_init) {
     if (!h.plan || h.S == 2 || h.K == 0 || tl.ntiles <= 0 || !fixed_grid(h.out_h, h.out_w)) return false;
-    if (!levels_buffered(t) || !levels_distinct(t)) return false;
+    if (!levels_buffered(t) || (zero_init && !levels_distinct(t))) return false;
+    // Adding a few samples, the scatter's one launch is shorter than the gather's two (one RoI of
+    // 256 channels, 7x7, one sample: 17.2 against 20.7 us a call; four 18.3 against 20.1; eight
+    // 27.5 against 20.3).
+    if (!zero_init && h.S > 0 && static_cast<double>(h.K) * t.C * h.out_h * h.out_w * h.S * h.S <= 65536.0)
+        return false;
     const double side = static_cast<double>(int64_t(1) << (tl.shift - 3));
     return tl.ntiles * (side * side / 4) * ((t.C + 63) / 64) < double(1 << 24);
 }
@@ -714,7 +727,7 @@ re_status_t bwd_head(const BwdHead &h, const LevelTable &t, bool cl, const int64
     const bool gather_ok = head_gather_ok(h, t, tl);
     if (algorithm == RE_BWD_GATHER && !gather_ok && h.K > 0) return RE_ERR_UNSUPPORTED;
     if ((gather_ok && algorithm != RE_BWD_SCATTER) ||
-        (algorithm == RE_BWD_AUTO && head_gather_any_ok(h, t, tl)))
+        (algorithm == RE_BWD_AUTO && head_gather_any_ok(h, t, tl, zero_init)))
         return from_hip(launch_gather(gather_args(t, h, tl, zero_init), h.gdt, s));
     re_status_t st;
     if (zero_init) {

@@ -205,3 +205,45 @@ def test_non_finite_gradient_on_integer_samples(P, S, zero_init, dt):
         g = g.to(torch.bfloat16)
     s = _as_the_scatter(rois, g, P, S, True, "cl", zero_init)
     assert np.isnan(s[0]).any() and np.isposinf(s[0]).any() and np.isneginf(s[0]).any()
+
+
+def _adds(rois, S, streams):
+    """Every stream adds one upstream gradient into one pyramid; the sum against the oracle."""
+    rng, feats, dev, r, lv, ws, lv_np = _setup(rois, SHAPES, SCALES, "f32", "cl")
+    g = rng.standard_normal((len(streams), rois.shape[0], 70, 7, 7), dtype=np.float32)
+    gd = torch.from_numpy(g).cuda()
+    grads = [torch.full(s, 7.0, device="cuda").contiguous(memory_format=torch.channels_last) for s in SHAPES]
+    torch.cuda.synchronize()
+    for i, st in enumerate(streams):
+        rex.roi_align_bwd(gd[i], r, lv, (7, 7), S, True, grads, SCALES, zero_init=False,
+                          workspace=ws, stream=st)
+    torch.cuda.synchronize()
+    for l in range(len(SHAPES)):
+        ref = sum(oracle.roi_align_bwd(x.astype(np.float64), SHAPES, SCALES, rois, lv_np, 7, 7, S, True,
+                                       "parity")[l] for x in g)
+        aref = sum(oracle.roi_align_bwd(np.abs(x).astype(np.float64), SHAPES, SCALES, rois, lv_np, 7, 7, S,
+                                        True, "parity")[l] for x in g)
+        # (7 and the partial sums round to binary32: 2^-20 of them covers the few additions)
+        check_bwd(from_device(grads[l]) - 7.0, ref, aref + 7.0 * 2.0 ** -20 / 1e-4, False, "added")
+
+
+@pytest.mark.parametrize("S", [0, 3])
+def test_accumulating_calls_may_overlap(S):
+    # calls that add into one pyramid on several streams lose nothing (atomics, as the scatter)
+    _adds(_mixed_rois(), S, [torch.cuda.Stream() for _ in range(4)] * 2)
+
+
+def test_levels_that_share_memory():
+    # one tensor as two levels: both levels' gradients end up in it, which a gather that stores
+    # every element cannot do
+    rois = np.concatenate([_mixed_rois(), np.array([[0, 10, 0, 200, 98], [1, 100, 5, 300, 95]], np.float32)])
+    shapes, scales = [SHAPES[0], SHAPES[0]], [0.25, 0.25]
+    rng, feats, dev, r, lv, ws, lv_np = _setup(rois, shapes, scales, "f32", "cl")
+    assert 0 < int((lv_np == 1).sum()) < rois.shape[0]
+    g = rng.standard_normal((rois.shape[0], 70, 7, 7), dtype=np.float32)
+    grad = torch.full(shapes[0], 7.0, device="cuda").contiguous(memory_format=torch.channels_last)
+    rex.roi_align_bwd(torch.from_numpy(g).cuda(), r, lv, (7, 7), 3, True, [grad, grad], scales,
+                      zero_init=True, workspace=ws)
+    refs = [sum(oracle.roi_align_bwd(x.astype(np.float64), shapes, scales, rois, lv_np, 7, 7, 3, True,
+                                     "parity")) for x in (g, np.abs(g))]
+    check_bwd(from_device(grad), refs[0], refs[1], False, "shared levels")
