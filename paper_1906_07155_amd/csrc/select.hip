@@ -16,7 +16,8 @@
 //                        of their category (as box_nms does), boxes and scores in rank order
 //   greedy: sel_overlap_kernel and sel_resolve_kernel, the suppression of nms.hpp with a
 //                        workgroup per category deciding its boxes
-//   Soft-NMS: sel_soft_kernel, one wave (up to 512 candidates) or 16 per category
+//   Soft-NMS: sel_soft_kernel, per category one wave up to 64 candidates, 8 up to 512, 16 up
+//                        to 4096
 // Past those limits (or with a smaller workspace):
 //   nmsb_clear / count / scan / place_kernel, nmsb_select_kernel
 //                        counting, placement, and one 1024-thread workgroup per category
@@ -781,8 +782,14 @@ __device__ __forceinline__ void sel_soft(const NmsBatchArgs &a, int c, int base,
     if (threadIdx.x == 0) a.num_keep[c] = kept;
 }
 
-// One candidate per lane while 16 waves hold them (80 categories of 310: 108 us with one wave
-// and five candidates per lane, 91 with 16 waves, 77 with 8).
+// One candidate per lane while 16 waves hold them, in one wave up to 64 candidates and in 8 up
+// to 512 (80 categories of 310: 108 us with one wave and five candidates per lane, 91 with 16
+// waves, 77 with 8); four per lane up to 4096; a longer category is walked by select_category.
+//
+// The waves a category does not need end before the first barrier, and nothing follows the
+// selection: the hardware's barrier waits for the waves of a workgroup that have not ended
+// (CDNA instruction set guides, s_barrier).  Kept to the barriers instead, eight idle waves cost
+// each of the selections (80 categories of 310: 91 -> 106 us for the call).
 __global__ __launch_bounds__(kSelThreads) void sel_soft_kernel(NmsBatchArgs a, float share) {
     union Smem {
         SoftSmem<1> s1;
@@ -793,17 +800,13 @@ __global__ __launch_bounds__(kSelThreads) void sel_soft_kernel(NmsBatchArgs a, f
     const int c = static_cast<int>(blockIdx.x);
     const int base = a.start[c];
     const int n = a.start[c + 1] - base;
-    if (n <= 64) {
-        if (threadIdx.x < 64) sel_soft<1, 1>(a, c, base, n, share, sm.s1);
-    } else if (n <= 512) {
-        if (threadIdx.x < 512) sel_soft<8, 1>(a, c, base, n, share, sm.s1);
-    } else if (n <= 1024) {
-        sel_soft<16, 1>(a, c, base, n, share, sm.s1);
-    } else if (n <= 4096) {
-        sel_soft<16, 4>(a, c, base, n, share, sm.s4);
-    } else {
-        select_category(a, c, sm.lds);
-    }
+    const int threads = n <= 64 ? 64 : n <= 512 ? 512 : kSelThreads;
+    if (static_cast<int>(threadIdx.x) >= threads) return;   // whole waves
+    if (n <= 64) sel_soft<1, 1>(a, c, base, n, share, sm.s1);
+    else if (n <= 512) sel_soft<8, 1>(a, c, base, n, share, sm.s1);
+    else if (n <= 1024) sel_soft<16, 1>(a, c, base, n, share, sm.s1);
+    else if (n <= 4096) sel_soft<16, 4>(a, c, base, n, share, sm.s4);
+    else select_category(a, c, sm.lds);
 }
 
 static hipError_t launch_sel(const NmsBatchArgs &a, hipStream_t stream) {
