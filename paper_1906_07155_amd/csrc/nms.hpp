@@ -10,13 +10,14 @@
 //                  a list with their row and word index.
 //   resolve_rows   one workgroup decides all boxes.  The definition fixes a box as soon as
 //                  every box it overlaps is decided (removed by a kept one, kept if there is
-//                  none), so each round looks at all listed words of undecided boxes at once
-//                  and then lets every block of 64 decide what it can, its own overlaps by
-//                  ballots.  The lowest undecided block depends on decided boxes only, so a
-//                  round decides all of it: at most as many rounds as blocks, in practice the
-//                  length of the longest chain of overlaps (4 to 6).  Walking the blocks one
-//                  after the other costs two barriers and up to 64 dependent steps for each
-//                  (8192 boxes: 461 us against 23 us).
+//                  none), so the waves take the blocks of 64 in turn without a barrier between
+//                  them: each reads its block's listed words once, sees in LDS what the other
+//                  waves have decided, waits only for the boxes it depends on, and decides its
+//                  own overlaps by ballots.
+//                  (8192 boxes of two images that hardly overlap: 22 us; around 10 objects an
+//                  image, 300 thousand listed words: the call 300 us.  All words again in every
+//                  round, barriers between the rounds: 22 us, the call 4150; one block after the
+//                  other, barriers for each: 461 us, the call 445.)
 #pragma once
 
 #include "internal.hpp"
@@ -200,140 +201,229 @@ __device__ __forceinline__ void overlap_rows(const float4 *boxes, const int32_t 
     if (threadIdx.x == 0 && n > 64) out.len[(ib << lg) + s] = *count;
 }
 
-// Up to M blocks per wave: n <= 1024 M boxes; kCap listed words in LDS (the rest, if any, are
-// read from memory in every round).
+// OR over the 64 lanes (uniform), in DPP moves (see wave_inclusive_scan).
+__device__ __forceinline__ uint32_t wave_or_u32(uint32_t x) {
+    int v = static_cast<int>(x);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(v, 63));
+}
+// Bits `row` of the lanes with `on`.
+__device__ __forceinline__ uint64_t wave_rows(bool on, int row) {
+    if (__ballot(on) == 0) return 0;
+    const uint64_t bit = on ? uint64_t(1) << row : 0;
+    return static_cast<uint64_t>(wave_or_u32(static_cast<uint32_t>(bit >> 32))) << 32 |
+           wave_or_u32(static_cast<uint32_t>(bit));
+}
+
+// Up to M blocks per wave: n <= 1024 M boxes.
+constexpr int kNmsResolveThreads = 1024;
+constexpr int kNmsResolveWaves = kNmsResolveThreads / 64;
+constexpr int kNmsWaiting = 256;    // words of a block that wait, per wave
 template <int M>
 struct ResolveSmem {
-    static constexpr int kCap = 1536 * M;
-    uint64_t kept[16 * M];
-    uint64_t done[16 * M];       // decided boxes
-    uint64_t rem[16 * M];        // a kept box overlaps
-    uint64_t pend[16 * M];       // an undecided box overlaps
-    uint64_t word[kCap];
-    uint16_t col[kCap];          // the word's index
-    uint16_t row[kCap];          // its box
-    int32_t first[(16 * M << kNmsSplitLog) + 1];   // each list's first entry
-    int32_t part[40];
+    uint64_t kept[kNmsResolveWaves * M];   // decided boxes of each block: kept, and
+    uint64_t gone[kNmsResolveWaves * M];   // removed
+    int32_t len[kNmsResolveWaves * M << kNmsSplitLog];
+    uint64_t word[kNmsResolveWaves][kNmsWaiting];
+    uint16_t tag[kNmsResolveWaves][kNmsWaiting];
 };
 
+// A word of other waves' LDS state.  Bits of kept and gone are only ever set, each by the one
+// wave that has the block, so a reader needs no order between them: a bit not seen yet reads as
+// undecided and is looked at again.
+__device__ __forceinline__ uint64_t nms_peek(const uint64_t &x) {
+    return __hip_atomic_load(&x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void nms_post(uint64_t &x, uint64_t v) {
+    __hip_atomic_store(&x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // Decides the n boxes; sm.kept holds the result after the call.  By 1024 threads: wave w has
-// blocks w, w + 16, ..., lane = box.
-constexpr int kNmsResolveThreads = 1024;
-template <int M>
-__device__ __forceinline__ void resolve_rows(uint64_t *ws, int n, int lg, ResolveSmem<M> &sm) {
-    constexpr int kWaves = kNmsResolveThreads / 64;
-    constexpr int kCap = ResolveSmem<M>::kCap;
-    static_assert(kNmsResolveThreads == kPlanThreads, "block_exclusive_scan's workgroup");
+// blocks w, w + 16, ... in this order, lane = box.  A block's listed words are read once: a word
+// with a kept box removes its row, one whose boxes are all removed is done with, and one with
+// undecided boxes waits in LDS.  Then the wave looks at the waiting words of its undecided rows
+// until all rows are decided, which needs blocks before its own only: of the blocks not decided,
+// the first is the one its wave works on, and nothing it waits for is left, so every wait ends.
+// The scan of a block ends when its rows are all removed, as in a crowd they soon are.
+template <int M, int LG>
+__device__ __forceinline__ void resolve_rows(uint64_t *ws, int n, ResolveSmem<M> &sm) {
+    constexpr int kWaves = kNmsResolveWaves;
+    constexpr int kLists = 1 << LG;
+    constexpr int kGroup = 4;   // loads of 64 words in flight
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = uniform_i(tid >> 6);
     const int nb = (n + 63) >> 6;
-    const int nl = nb > 1 ? nb << lg : 0;
-    const int sp = (1 << lg) - 1;
     const NmsLists in = nms_lists(ws, n);
-    uint64_t own[M];
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-        const int i = (wave + kWaves * m) * 64 + lane;
-        own[m] = i < n ? in.own[i] : 0;
-    }
     for (int w = tid; w < kWaves * M; w += kNmsResolveThreads) {
         sm.kept[w] = 0;
-        sm.done[w] = 0;
-        sm.rem[w] = 0;
-        sm.pend[w] = 0;
+        sm.gone[w] = 0;
     }
-    // (a length is at most the list's room: block b's rows by its words)
-    for (int l = tid; l < nl; l += kNmsResolveThreads)
-        sm.first[l] = max(0, min(in.len[l], 64 * nms_split_words(l >> lg, l & sp, lg)));
+    // (a length is at most the list's room: block b's rows by its words; one block has no lists)
+    for (int l = tid; l < nb << LG; l += kNmsResolveThreads)
+        sm.len[l] = nb > 1 ? max(0, min(in.len[l], min(64, n - 64 * (l >> LG)) *
+                                                       nms_split_words(l >> LG, l & (kLists - 1), LG)))
+                           : 0;
     __syncthreads();
-    const int total = block_exclusive_scan(sm.first, nl, sm.part);
-    if (tid == 0) sm.first[nl] = total;
-    __syncthreads();
-    // entry e: its word, word index and box
-    auto entry = [&](int e, uint64_t &x, int &w, int &i) {
-        int lo = 0, hi = nl;   // the list that holds e: first[lo] <= e < first[hi]
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (sm.first[mid] <= e) lo = mid;
-            else hi = mid;
-        }
-        const int at = nms_list_base(n, lo >> lg, lo & sp, lg) + e - sm.first[lo];
-        const int t = in.tag[at];
-        x = in.word[at];
-        w = min(t >> 6, lo >> lg);
-        i = min((lo >> lg) * 64 + (t & 63), n - 1);
+
+    // A block's lists as one sequence: list s holds the entries from end[s - 1] to end[s].
+    struct Lists {
+        int b, total;
+        int end[kLists];
     };
-    const int held = min(total, kCap);
-    for (int e0 = tid; e0 < held; e0 += 4 * kNmsResolveThreads) {
+    auto lists_of = [&](int b, Lists &q) {
+        q.b = b;
+        q.total = 0;
+        if (b >= nb) return;
+        const int incl = wave_inclusive_scan(lane < kLists ? sm.len[(b << LG) + (lane & (kLists - 1))] : 0, lane);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = e0 + u * kNmsResolveThreads;
-            if (e < held) {
-                uint64_t x;
-                int w, i;
-                entry(e, x, w, i);
-                sm.word[e] = x;
-                sm.col[e] = static_cast<uint16_t>(w);
-                sm.row[e] = static_cast<uint16_t>(i);
+        for (int s = 0; s < kLists; ++s) q.end[s] = __builtin_amdgcn_readlane(incl, s);
+        q.total = q.end[kLists - 1];
+    };
+    struct Group {
+        uint64_t x[kGroup];
+        int t[kGroup];
+    };
+    auto load = [&](const Lists &q, int e0, Group &g) {   // entries [e0, e0 + 64 kGroup)
+        const int rows = min(64, n - 64 * q.b);
+#pragma unroll
+        for (int u = 0; u < kGroup; ++u) {
+            g.x[u] = 0;
+            g.t[u] = 0;
+            if (e0 + 64 * u >= q.total) continue;
+            const int e = e0 + 64 * u + lane;
+            int s = 0, from = 0;
+#pragma unroll
+            for (int l = 0; l + 1 < kLists; ++l) {
+                s += e >= q.end[l] ? 1 : 0;
+                from = e >= q.end[l] ? q.end[l] : from;
+            }
+            if (e < q.total) {
+                const int at = 32 * q.b * (q.b - 1) + e - from +
+                               rows * (s * (q.b >> LG) + min(s, q.b & (kLists - 1)));
+                g.x[u] = in.word[at];
+                g.t[u] = in.tag[at];
             }
         }
-    }
-    uint64_t und[M], kb[M];          // uniform: undecided and kept boxes of the block
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-        const int rows = min(64, n - (wave + kWaves * m) * 64);
-        und[m] = rows >= 64 ? ~uint64_t(0) : rows > 0 ? (uint64_t(1) << rows) - 1 : 0;
-        kb[m] = 0;
-    }
-    int left;
-    do {
-        __syncthreads();   // the last round's verdicts (or the entries) are in LDS
-        // every listed word of an undecided box against the decided ones
-        auto look = [&](uint64_t x, int w, int i) {
-            const uint64_t bit = uint64_t(1) << (i & 63);
-            if (sm.done[i >> 6] & bit) return;
-            if (x & sm.kept[w])
-                atomicOr(reinterpret_cast<unsigned long long *>(&sm.rem[i >> 6]), bit);
-            else if (x & ~sm.done[w])
-                atomicOr(reinterpret_cast<unsigned long long *>(&sm.pend[i >> 6]), bit);
+    };
+
+    uint64_t *const wword = sm.word[wave];
+    uint16_t *const wtag = sm.tag[wave];
+    auto own_of = [&](int b) { return b * 64 + lane < n ? in.own[b * 64 + lane] : uint64_t(0); };
+    Lists cur;
+    Group grp;
+    lists_of(wave, cur);
+    uint64_t own = wave < nb ? own_of(wave) : 0;
+    load(cur, 0, grp);
+    for (int b = wave; b < nb; b += kWaves) {
+        const int rows = min(64, n - 64 * b);
+        const uint64_t all = rows >= 64 ? ~uint64_t(0) : (uint64_t(1) << rows) - 1;
+        uint64_t U = all, K = 0;   // uniform: the block's undecided and kept boxes
+        Lists nxt;
+        lists_of(b + kWaves, nxt);
+        const uint64_t own_next = b + kWaves < nb ? own_of(b + kWaves) : 0;
+        int waiting = 0;
+        // One word of row t & 63, of block t >> 6's boxes: removes the row, waits or neither.
+        auto look = [&](uint64_t x, int t, bool &rem, bool &wait) {
+            const int w = min(t >> 6, b - 1);
+            const bool on = x != 0 && ((U >> (t & 63)) & 1);
+            const uint64_t k = on ? nms_peek(sm.kept[w]) : 0;
+            const uint64_t g = on ? nms_peek(sm.gone[w]) : 0;
+            rem = (x & k) != 0;
+            wait = on && !rem && (x & ~g) != 0;
         };
-        for (int e = tid; e < held; e += kNmsResolveThreads) look(sm.word[e], sm.col[e], sm.row[e]);
-        for (int e = held + tid; e < total; e += kNmsResolveThreads) {
-            uint64_t x;
-            int w, i;
-            entry(e, x, w, i);
-            look(x, w, i);
-        }
-        __syncthreads();
-        bool more = false;
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-            if (und[m] == 0) continue;
-            const int b = wave + kWaves * m;
-            uint64_t U = und[m] & ~sm.rem[b];
-            uint64_t K = kb[m];
-            const uint64_t P = sm.pend[b];
+        auto put = [&](uint64_t x, int t, bool wait, int at) {
+            const uint64_t m = __ballot(wait);
+            const int p = at + __popcll(m & ((uint64_t(1) << lane) - 1));
+            if (wait) {
+                wword[p] = x;
+                wtag[p] = static_cast<uint16_t>(t);
+            }
+            return __popcll(m);
+        };
+        // Another look at the waiting words; returns the rows that still wait.
+        auto sweep = [&]() {
+            uint64_t pend = 0;
+            int left = 0;
+            wave_sync();
+            for (int e = 0; e < waiting; e += 64) {
+                const bool in_queue = e + lane < waiting;
+                const uint64_t x = in_queue ? wword[e + lane] : 0;
+                const int t = in_queue ? wtag[e + lane] : 0;
+                bool rem, wait;
+                look(x, t, rem, wait);
+                wave_sync();   // read before the words before them move down
+                U &= ~wave_rows(rem, t & 63);
+                pend |= wave_rows(wait, t & 63);
+                left += put(x, t, wait, left);
+            }
+            waiting = left;
+            wave_sync();
+            return pend;
+        };
+        // What the block can decide itself, but for the rows in pend, and the word of it.
+        auto decide = [&](uint64_t pend) {
             for (;;) {
                 const bool on = (U >> lane) & 1;
-                const uint64_t rm = __ballot(on && (own[m] & K) != 0);
+                const uint64_t rm = __ballot(on && (own & K) != 0);
                 U &= ~rm;
-                const uint64_t kn = __ballot(on && (own[m] & (U | K)) == 0) & U & ~P;
+                const uint64_t kn = __ballot(on && (own & (U | K)) == 0) & U & ~pend;
                 K |= kn;
                 U &= ~kn;
                 if ((rm | kn) == 0) break;
             }
-            und[m] = U;
-            kb[m] = K;
             if (lane == 0) {
-                sm.kept[b] = K;
-                sm.done[b] = ~U;
-                sm.pend[b] = 0;
+                nms_post(sm.kept[b], K);
+                nms_post(sm.gone[b], all & ~(U | K));
             }
-            more = more || U != 0;
+        };
+
+        const Group g0 = grp;
+        if (cur.total <= 64) {   // few overlaps: the words stay in registers
+            load(nxt, 0, grp);
+            for (;;) {
+                bool rem, wait;
+                look(g0.x[0], g0.t[0], rem, wait);
+                const uint64_t before = U;
+                U &= ~wave_rows(rem, g0.t[0] & 63);
+                decide(wave_rows(wait, g0.t[0] & 63));
+                if (U == 0) break;
+                if (U == before) __builtin_amdgcn_s_sleep(1);
+            }
+        } else {
+            bool fetched = false;   // grp holds the next block's first words
+            for (int e0 = 0; e0 < cur.total && U != 0; e0 += 64 * kGroup) {
+                const Group g = grp;
+                const bool more = e0 + 64 * kGroup < cur.total;
+                load(more ? cur : nxt, more ? e0 + 64 * kGroup : 0, grp);
+                fetched = !more;
+#pragma unroll
+                for (int u = 0; u < kGroup; ++u) {
+                    if (e0 + 64 * u >= cur.total) continue;
+                    while (waiting > kNmsWaiting - 64) sweep();
+                    bool rem, wait;
+                    look(g.x[u], g.t[u], rem, wait);
+                    U &= ~wave_rows(rem, g.t[u] & 63);
+                    waiting += put(g.x[u], g.t[u], wait, waiting);
+                }
+            }
+            if (!fetched) load(nxt, 0, grp);
+            for (;;) {
+                const uint64_t before = U;
+                decide(waiting > 0 ? sweep() : 0);
+                if (U == 0) break;
+                if (U == before) __builtin_amdgcn_s_sleep(1);
+            }
         }
-        left = __syncthreads_or(more);
-    } while (left);
+        cur = nxt;
+        own = own_next;
+    }
+    __syncthreads();
 }
 
 // Kept boxes of all blocks, and those before block b (every lane of a wave).

@@ -604,7 +604,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_resolve_kernel(NmsBatchArgs a
     const int64_t out = static_cast<int64_t>(c) * limit;
     int count = 0;
     if (n > 0) {
-        resolve_rows<M>(a.words + a.wfirst[c], n, kSelSplitLog, sm.r);
+        resolve_rows<M, kSelSplitLog>(a.words + a.wfirst[c], n, sm.r);
         const int lane = threadIdx.x & 63;
         const int nb = (n + 63) >> 6;
         for (int b = static_cast<int>(threadIdx.x) >> 6; b < nb; b += kSelWaves) {

@@ -46,5 +46,22 @@ def build(outdir: str, edit=None) -> str:
     return out
 
 
+def build_nms(outdir: str) -> str:
+    """Compile the emulator of nms.hpp's resolve_rows (``emu_nms.cpp``) into outdir."""
+    src = open(os.path.join(CSRC, "nms.hpp")).read()
+    # the layout of the lists, then the deciding half (overlap_rows stays out)
+    a, b = src.index("// The words of a row block are dealt"), src.index("// IoU > t (t >= 0) needs")
+    c, d = src.index("// OR over the 64 lanes"), src.index("// Kept boxes of all blocks")
+    with open(os.path.join(outdir, "nms_resolve.inc"), "w") as f:
+        f.write('#include "internal.hpp"\nnamespace rex {\n' + src[a:b] + src[c:d] + "}\n")
+    out = os.path.join(outdir, "nms_emu")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-g", "-Wno-attributes",
+                           "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
+                           "-fno-omit-frame-pointer", "-I" + HERE, "-I" + outdir, "-I" + CSRC,
+                           "-I" + os.path.join(ROOT, "include"),
+                           os.path.join(HERE, "emu_nms.cpp"), "-o", out])
+    return out
+
+
 if __name__ == "__main__":
     print(build(sys.argv[1] if len(sys.argv) > 1 else os.getcwd()))

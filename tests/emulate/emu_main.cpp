@@ -107,6 +107,17 @@ unsigned long long __ballot(int pred) {
     return m;
 }
 
+int emu_readlane(int v, int lane) {
+    const int *vals;
+    const bool *act;
+    wave_xchg(v, vals, act);
+    if (!act[lane]) {
+        std::printf("a read of an inactive lane\n");
+        std::abort();
+    }
+    return vals[lane];
+}
+
 // Runs one workgroup of n work-items to completion.
 static void run_block(int n) {
     if (!g_stacks) {
@@ -218,6 +229,7 @@ template <typename F> static void launch(int grid, int threads, size_t smem_word
     }
 }
 
+#ifndef EMU_CORE_ONLY
 // The kernels (plan.hip without its launchers, generated) and the host code.
 #include "plan_kernels.inc"
 #include "api.hip"
@@ -365,3 +377,4 @@ int main(int argc, char **argv) {
     std::printf("done\n");
     return 0;
 }
+#endif   // EMU_CORE_ONLY

@@ -36,6 +36,12 @@ unsigned long long __ballot(int pred);
 inline int __popcll(unsigned long long v) { return __builtin_popcountll(v); }
 int emu_update_dpp(int old, int src, int ctrl, int row_mask, int bank_mask, bool bound);
 #define __builtin_amdgcn_update_dpp(o, s, c, r, b, bc) emu_update_dpp(o, s, c, r, b, bc)
+int emu_readlane(int v, int lane);
+#define __builtin_amdgcn_readlane(v, l) emu_readlane(v, l)
+#define __builtin_amdgcn_s_sleep(n)
+#define __HIP_MEMORY_SCOPE_WORKGROUP 0
+#define __hip_atomic_load(p, order, scope) (*(p))
+#define __hip_atomic_store(p, v, order, scope) (*(p) = (v))
 inline float __builtin_amdgcn_rcpf(float x) { return 1.0f / x; }
 inline int __builtin_amdgcn_readfirstlane(int v) { return v; }
 typedef struct { int w[4]; } __amdgpu_buffer_rsrc_t;
@@ -43,7 +49,7 @@ typedef struct { int w[4]; } __amdgpu_buffer_rsrc_t;
 #define __builtin_amdgcn_raw_buffer_load_b32(...) 0u
 #define __builtin_amdgcn_raw_buffer_load_b16(...) 0u
 #define __builtin_amdgcn_fence(...)
-#define __builtin_amdgcn_wave_barrier()
+#define __builtin_amdgcn_wave_barrier() ((void)__ballot(1))   /* the lanes of a wave keep step */
 #define __builtin_amdgcn_ballot_w64(p) __ballot(p)
 #define __builtin_amdgcn_mbcnt_lo(a, b) 0
 #define __builtin_amdgcn_mbcnt_hi(a, b) 0

@@ -49,6 +49,24 @@ def test_dense_lists():
     run("identical", np.tile(b[:1], (700, 1)), np.full(700, 0.5, np.float32), 0.9)
 
 
+@pytest.mark.parametrize("objects,jitter", [(10, 0.1), (20, 0.15), (3, 0.05)])
+@pytest.mark.parametrize("thr", [0.5, 0.7])
+def test_crowds(objects, jitter, thr):
+    # the largest call, its boxes around a few objects of each image as a detector's proposals
+    # are: hundreds of thousands of overlap words, nearly all boxes removed, and rows that wait
+    # for more words than a wave keeps
+    rng = np.random.default_rng(objects)
+    b = []
+    for _ in range(2):
+        c = rng.uniform(0, (1333, 800), (objects, 2))
+        wh = np.exp(rng.uniform(np.log(40), np.log(400), (objects, 2)))
+        o = rng.integers(0, objects, 4096)
+        b.append(np.concatenate([c - wh / 2, c + wh / 2], 1)[o] +
+                 rng.uniform(-jitter, jitter, (4096, 4)) * np.tile(wh[o], 2))
+    run("crowds", np.concatenate(b).astype(np.float32), rng.uniform(0, 1, 8192).astype(np.float32), thr,
+        cats=np.repeat(np.arange(2, dtype=np.int32), 4096))
+
+
 @pytest.mark.parametrize("shift", [1, 64, 65])
 def test_chains(shift):
     # box r overlaps only boxes r - shift and r + shift in rank order: every decision waits
