@@ -468,9 +468,10 @@ re_status_t box_nms(const float *boxes, const float *scores, const int32_t *cate
  *   A workspace of the 48 bytes per box alone is accepted too: the call then takes the
  *   slower form below.
  * Within those limits the whole GPU ranks the candidates and finds the overlaps, and a
- * workgroup per category decides (greedy: all boxes whose overlaps are decided at once;
+ * workgroup per category decides (greedy: every box once those it overlaps are decided;
  * Soft-NMS: one iteration per selection).  Beyond them, and for single categories past
- * the room for their lists (greedy) or 4096 candidates (Soft-NMS), a category is sorted
+ * 8192 candidates or the room for lists (greedy; all categories share it, and by index
+ * those that still fit get theirs) or 4096 candidates (Soft-NMS), a category is sorted
  * and walked in order by one workgroup.  Results are the same. */
 #define RE_NMS_HARD 0
 #define RE_NMS_LINEAR 1

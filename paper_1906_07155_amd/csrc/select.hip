@@ -206,12 +206,20 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
     return v;
 }
 
-// Greedy NMS over the sorted candidates [base, base + n) of category c.
+// Greedy NMS over the sorted candidates [base, base + n) of category c, 64 at a time: every wave
+// tests them against its share of the kept list and of their own pairs, one wave decides.  The
+// kept list is in LDS up to kKeptLds boxes, beyond that in the workspace.  (One wave for the
+// pairs and the kept list in the workspace, 32 categories of 8000 boxes: 1948 us against 999.)
+constexpr int kKeptLds = kSegLds / 2 - 100;
 __device__ void select_greedy(const NmsBatchArgs &a, int c, int base, int n, uint64_t *lds) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    float4 *cand = reinterpret_cast<float4 *>(lds);                    // [64] the block
-    unsigned long long *hit = reinterpret_cast<unsigned long long *>(cand + 64);   // [1]
+    float4 *kl = reinterpret_cast<float4 *>(lds);                      // [kKeptLds]
+    float4 *cand = kl + kKeptLds;                                      // [64] the block
+    uint64_t *over = reinterpret_cast<uint64_t *>(cand + 64);          // [64] its earlier overlaps
+    unsigned long long *hit = reinterpret_cast<unsigned long long *>(over + 64);   // [1]
     int32_t *s_kept = reinterpret_cast<int32_t *>(hit + 1);            // [1]
+    static_assert((kKeptLds + 64) * sizeof(float4) + 66 * sizeof(uint64_t) <= kSegLds * sizeof(uint64_t),
+                  "select_category's LDS");
     const int limit = a.max_keep;
     int kept = 0;
     for (int b0 = 0; b0 < n && kept < limit; b0 += 64) {
@@ -219,53 +227,47 @@ __device__ void select_greedy(const NmsBatchArgs &a, int c, int base, int n, uin
         if (tid < 64 && tid < nb) cand[tid] = a.sbox[base + b0 + tid];
         if (tid == 0) *hit = 0;
         __syncthreads();
-        // every wave tests the block against its share of the kept list
         {
             const float4 mine = lane < nb ? cand[lane] : make_float4(0, 0, 0, 0);
             bool h = false;
-            for (int k = wave; k < kept; k += kSelWaves) {
-                const float4 kb = a.kbox[base + k];
-                h = h || (nms_iou(kb, mine) > a.iou_threshold);
-            }
+            for (int k = wave; k < min(kept, kKeptLds); k += kSelWaves)
+                h = h || (nms_iou(kl[k], mine) > a.iou_threshold);
+            for (int k = kKeptLds + wave; k < kept; k += kSelWaves)
+                h = h || (nms_iou(a.kbox[base + k], mine) > a.iou_threshold);
             const uint64_t bits = __ballot(h && lane < nb);
             if (lane == 0 && bits) atomicOr(hit, static_cast<unsigned long long>(bits));
+            // bit t of over[u] marks an earlier candidate t of the block that would remove u
+            for (int u = wave; u < nb; u += kSelWaves) {
+                const uint64_t m = __ballot(lane < u && nms_iou(mine, cand[u]) > a.iou_threshold);
+                if (lane == 0) over[u] = m;
+            }
         }
         __syncthreads();
         if (wave == 0) {
-            // the block's own overlaps: bit u of lane t marks a later candidate u of the
-            // block that candidate t removes
-            uint64_t dbits = 0;
-            if (lane < nb) {
-                const float4 mine = cand[lane];
-                for (int u = lane + 1; u < nb; ++u)
-                    if (nms_iou(mine, cand[u]) > a.iou_threshold) dbits |= uint64_t(1) << u;
-            }
+            const uint64_t own = lane < nb ? over[lane] : 0;
             const uint64_t h0 = *hit;
-            uint64_t rem = (static_cast<uint64_t>(static_cast<uint32_t>(
-                                __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(h0 >> 32))))
-                            << 32) |
-                           static_cast<uint32_t>(
-                               __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(h0)));
-            uint64_t keptm = 0;
-            int nk = kept;
-            for (int t = 0; t < nb && nk < limit; ++t) {
-                if (!((rem >> t) & 1)) {
-                    keptm |= uint64_t(1) << t;
-                    ++nk;
-                    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(dbits), t);
-                    const uint32_t hi =
-                        __builtin_amdgcn_readlane(static_cast<uint32_t>(dbits >> 32), t);
-                    rem |= (static_cast<uint64_t>(hi) << 32) | lo;
-                }
+            uint64_t U = ~((static_cast<uint64_t>(static_cast<uint32_t>(uniform_i(static_cast<int>(h0 >> 32))))
+                            << 32) | static_cast<uint32_t>(uniform_i(static_cast<int>(h0))));
+            if (nb < 64) U &= (uint64_t(1) << nb) - 1;
+            uint64_t K = 0;   // U: undecided, K: kept
+            for (;;) {
+                const bool on = (U >> lane) & 1;
+                const uint64_t rm = __ballot(on && (own & K) != 0);
+                U &= ~rm;
+                const uint64_t kn = __ballot(on && (own & (U | K)) == 0) & U;
+                K |= kn;
+                U &= ~kn;
+                if ((rm | kn) == 0) break;
             }
-            if ((keptm >> lane) & 1) {
-                const int r = kept + __popcll(keptm & ((uint64_t(1) << lane) - 1));
+            const int r = kept + __popcll(K & ((uint64_t(1) << lane) - 1));
+            if (((K >> lane) & 1) && r < limit) {
                 const int pos = base + b0 + lane;
-                a.kbox[base + r] = cand[lane];
+                if (r < kKeptLds) kl[r] = cand[lane];
+                else a.kbox[base + r] = cand[lane];
                 a.keep[static_cast<int64_t>(c) * limit + r] = a.sidx[pos];
                 a.kept_scores[static_cast<int64_t>(c) * limit + r] = a.sscore[pos];
             }
-            if (lane == 0) *s_kept = nk;
+            if (lane == 0) *s_kept = min(kept + __popcll(K), limit);
         }
         __syncthreads();
         kept = *s_kept;
@@ -378,10 +380,8 @@ __device__ void select_soft(const NmsBatchArgs &a, int c, int base, int n, uint6
     if (tid == 0) a.num_keep[c] = kept;
 }
 
-// One category by one workgroup: sorts its candidates and selects in order.
-__device__ void select_category(const NmsBatchArgs &a, int c, uint64_t *lds) {
-    const int base = a.start[c];
-    const int n = a.start[c + 1] - base;
+// Candidates [base, base + n) into rank order, with their boxes and scores.
+__device__ void sort_category(const NmsBatchArgs &a, int base, int n, uint64_t *lds) {
     // rank order: score rank key, then box index (unique keys)
     uint64_t *gkeys = a.skey + base;
     const bool in_lds = n <= kSegLds;
@@ -404,14 +404,21 @@ __device__ void select_category(const NmsBatchArgs &a, int c, uint64_t *lds) {
         a.sscore[base + r] = a.scores[i];
     }
     __syncthreads();   // sorted arrays complete; the LDS is reused below
+}
+
+// One category by one workgroup: sorts its candidates (unless sel_rank_kernel has) and selects in
+// order.
+__device__ void select_category(const NmsBatchArgs &a, int c, uint64_t *lds, bool sorted) {
+    const int base = a.start[c];
+    const int n = a.start[c + 1] - base;
+    if (!sorted) sort_category(a, base, n, lds);
     if (a.method == kNmsHard) select_greedy(a, c, base, n, lds);
     else select_soft(a, c, base, n, lds);
 }
-
 __global__ __launch_bounds__(kSelThreads) void nmsb_select_kernel(NmsBatchArgs a) {
     __shared__ uint64_t lds[kSegLds];   // sort keys, then the selection's working set
     for (int c = blockIdx.x; c < a.C; c += gridDim.x) {
-        select_category(a, c, lds);
+        select_category(a, c, lds, false);
         __syncthreads();   // before the next category reuses the LDS
     }
 }
@@ -503,8 +510,22 @@ __global__ __launch_bounds__(kSelThreads) void sel_place_kernel(NmsBatchArgs a, 
         const int w = n > 0 && n <= fast_n ? static_cast<int>(nms_words(n)) : 0;
         if (tid < a.C) tab[tid] = w;
         __syncthreads();
-        block_exclusive_scan(tab, a.C, part);
-        if (tid < a.C) a.wfirst[tid] = w > 0 && tab[tid] + w <= a.word_cap ? tab[tid] : -1;
+        if (block_exclusive_scan(tab, a.C, part) <= a.word_cap) {
+            if (tid < a.C) a.wfirst[tid] = w > 0 ? tab[tid] : -1;
+        } else {
+            // not room for all: in index order, every category that still fits
+            if (tid < a.C) tab[tid] = w;
+            __syncthreads();
+            if (tid == 0) {
+                int at = 0;
+                for (int c = 0; c < a.C; ++c) {
+                    const int words = tab[c];
+                    const bool fits = words > 0 && at + words <= a.word_cap;
+                    a.wfirst[c] = fits ? at : -1;
+                    at += fits ? words : 0;
+                }
+            }
+        }
     }
     if (tid < a.C) cur[tid] += before;
     __syncthreads();
@@ -586,10 +607,9 @@ __global__ __launch_bounds__(kNmsOverlapThreads) void sel_overlap_kernel(NmsBatc
     overlap_rows(a.sbox + base, nullptr, n, a.iou_threshold, share, a.words + w, ib, s, kSelSplitLog, &count);
 }
 
-template <int M>
 __global__ __launch_bounds__(kSelThreads) void sel_resolve_kernel(NmsBatchArgs a) {
     union Smem {
-        ResolveSmem<M> r;
+        ResolveSmem<8> r;
         uint64_t lds[kSegLds];
     };
     __shared__ Smem sm;
@@ -597,14 +617,14 @@ __global__ __launch_bounds__(kSelThreads) void sel_resolve_kernel(NmsBatchArgs a
     const int base = a.start[c];
     const int n = a.start[c + 1] - base;
     if (n > 0 && a.wfirst[c] < 0) {
-        select_category(a, c, sm.lds);
+        select_category(a, c, sm.lds, n <= kSegLds);
         return;
     }
     const int limit = a.max_keep;
     const int64_t out = static_cast<int64_t>(c) * limit;
     int count = 0;
     if (n > 0) {
-        resolve_rows<M, kSelSplitLog>(a.words + a.wfirst[c], n, sm.r);
+        resolve_rows<8, kSelSplitLog>(a.words + a.wfirst[c], n, sm.r);
         const int lane = threadIdx.x & 63;
         const int nb = (n + 63) >> 6;
         for (int b = static_cast<int>(threadIdx.x) >> 6; b < nb; b += kSelWaves) {
@@ -806,20 +826,17 @@ __global__ __launch_bounds__(kSelThreads) void sel_soft_kernel(NmsBatchArgs a, f
     else if (n <= 512) sel_soft<8, 1>(a, c, base, n, share, sm.s1);
     else if (n <= 1024) sel_soft<16, 1>(a, c, base, n, share, sm.s1);
     else if (n <= 4096) sel_soft<16, 4>(a, c, base, n, share, sm.s4);
-    else select_category(a, c, sm.lds);
+    else select_category(a, c, sm.lds, n <= kSegLds);
 }
 
 static hipError_t launch_sel(const NmsBatchArgs &a, hipStream_t stream) {
     const int ranges = (a.N + sel_range(a.N) - 1) / sel_range(a.N);
     const size_t cats = static_cast<size_t>(a.C) * sizeof(int32_t);
-    // greedy: a resolve workgroup of 8 blocks per wave has a CU's LDS to itself; with more
-    // categories than CUs, 2 blocks per wave (2048 candidates) let two share one
-    const int fast_n = a.C > 256 ? 2048 : kNmsMaxBoxes;
     hipError_t e;
     sel_count_kernel<<<ranges, kSelThreads, cats, stream>>>(a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     sel_place_kernel<<<ranges, kSelThreads, 2 * cats + 64 * sizeof(int32_t), stream>>>(
-        a, ranges, a.method == kNmsHard ? fast_n : 0);
+        a, ranges, a.method == kNmsHard ? kNmsMaxBoxes : 0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int blocks = a.N / 64 + a.C;   // at least the categories' blocks
     sel_rank_kernel<<<blocks, kSelRankThreads, 0, stream>>>(a);
@@ -832,8 +849,7 @@ static hipError_t launch_sel(const NmsBatchArgs &a, hipStream_t stream) {
     sel_overlap_kernel<<<blocks << kSelSplitLog, kNmsOverlapThreads, 0, stream>>>(
         a, nms_share(a.iou_threshold));
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (fast_n == kNmsMaxBoxes) sel_resolve_kernel<8><<<a.C, kSelThreads, 0, stream>>>(a);
-    else sel_resolve_kernel<2><<<a.C, kSelThreads, 0, stream>>>(a);
+    sel_resolve_kernel<<<a.C, kSelThreads, 0, stream>>>(a);
     return hipGetLastError();
 }
 

@@ -50,6 +50,22 @@ def test_registers_and_list_room(method):
     run("room " + method, b, s, c, len(sizes), method, thr=0.5, st=0.0, max_keep=150)
 
 
+def test_room_in_any_order():
+    # more list room asked for than there is: categories that do not fit are walked by one
+    # workgroup, smaller ones after them still get lists
+    sizes = [8192] * 4 + [100, 0, 64, 3000, 65]
+    b, s, c = _categories(sizes, 5, img=(800, 1333), sides=(4.0, 80.0))
+    run("order", b, s, c, len(sizes), "hard", thr=0.5, max_keep=500)
+    run("order, past the LDS", b, s, c, len(sizes), "hard", thr=0.9, max_keep=8192)
+
+
+def test_kept_list_past_the_lds():
+    # one category past the parallel form, with more kept boxes than the walk holds in LDS
+    b, s, c = _categories([20000], 6, img=(4000, 6000), sides=(4.0, 40.0))
+    for max_keep in (3995, 3996, 3997, 6000, 20000):
+        run("kept %d" % max_keep, b, s, c, 1, "hard", thr=0.5, max_keep=max_keep)
+
+
 @pytest.mark.parametrize("method", ["hard", "linear", "gaussian"])
 def test_one_workgroup_form(method):
     b, s, c = _categories(SIZES, 3)
