@@ -86,11 +86,11 @@ __device__ __forceinline__ float any_weight(const float *pos, const Axis &a, int
 
 // Positions of every sample of both axes into pos ([bin][sample] of the rows, then of the
 // columns at kAnyGrid * P), by the whole workgroup.
-template <int P>
+template <int P, int NT = 256>
 __device__ __forceinline__ void any_positions(const Axis &ay, const Axis &ax, int H, int W,
                                               float *pos) {
     const int ny = P * ay.grid, n = ny + P * ax.grid;
-    for (int e = threadIdx.x; e < n; e += 256) {
+    for (int e = threadIdx.x; e < n; e += NT) {
         const bool row = e < ny;
         const int u = row ? e : e - ny;
         const int g = row ? ay.grid : ax.grid;
@@ -110,10 +110,13 @@ __device__ __forceinline__ void any_positions(const Axis &ay, const Axis &ax, in
 // As the two-samples kernel (fwd.hip): wave w owns bin rows [w * RPW, (w + 1) * RPW) and
 // loads the pixel rows they tap times the RoI's columns, in chunks of CX columns with D
 // units (chunk, row) in flight; each row is weighted into the wave's bin rows, and at the
-// end of a chunk its columns are reduced into the bin columns that tap them.  Samples are
-// at most a pixel apart (a capped grid aside), so the tapped rows and columns are runs.
-// RoIs of more than kAnyCols columns or, per wave, kAnyRows rows are
-// walked in panels of that size (a box may span the whole map), each with its own weights.
+// end of a chunk its columns are reduced into the bin columns that tap them.  Rows and columns
+// are walked in panels of kAnyRows (per wave) and kAnyCols slots, each with its own weights (a
+// box may span the whole map).  A slot is a pixel row or column of the run from the first
+// tapped to the last, or, where the run is longer than the samples have taps (few samples in
+// wide bins: most of the run is not tapped), one tap of one sample.  (One 200 x 336 level, boxes
+// of 200 to 800 pixels at stride 4, 7x7, S = 1 / 3 / 4: 14 / 66 / 105 us, runs always: 253 /
+// 478 / 514, one thread per output element: 57 / 585 / 1120.)
 constexpr int kAnyCols = 64;
 constexpr int kAnyRows = 32;
 
@@ -138,26 +141,38 @@ __device__ __forceinline__ float any_value(const AnyPix<T, CPL> &p, int j) {
     else return __uint_as_float(j == 0 ? (p.w[0] << 16) : (p.w[0] & 0xffff0000u));
 }
 
-template <int P, int CHK>
+template <int P, int CHK, int NW>
 struct AnyFwdSmem {
     float pos[2 * P * kAnyGrid];
     __align__(16) float wx[P][kAnyCols];
-    __align__(16) float wy[4][kAnyRows][4];   // [wave][row][bin row of the wave]
+    __align__(16) float wy[NW][kAnyRows][NW == 4 ? 4 : 1];   // [wave][row][bin row of the wave]
     __align__(16) uint32_t xoff[kAnyCols];    // byte offsets of the panel's columns
     uint64_t hit[P];                          // columns of the panel a bin column taps
     __align__(16) float stile[CHK * P * P];
 };
 
+// Tap j of the samples at pos: sample j / 2, its lower pixel for even j, the upper one (the same
+// on the last pixel, with weight zero) for odd j; false for a sample off the map.
+__device__ __forceinline__ bool any_tap(const float *pos, int j, int size, int &pixel, float &w) {
+    const float v = pos[j >> 1];
+    const int l = static_cast<int>(v);
+    const float f = v - static_cast<float>(l);
+    pixel = (j & 1) ? min(l + 1, size - 1) : l;
+    w = (j & 1) ? f : 1.0f - f;
+    return v >= 0.0f;
+}
+
 // Column offsets come from an LDS table and not from registers kept over a chunk's rows (the
 // registers cost a wave per SIMD: 70 us against 44 us on the batch above); five waves per
 // SIMD by spilling 12 registers is slower too (50 us).
-template <typename T, typename TO, int P, int CX, int CHK, int CPL, int D>
-__global__ __launch_bounds__(256) void fwd_any_kernel(FwdArgs args) {
+template <typename T, typename TO, int P, int CX, int CHK, int CPL, int D, int NW>
+__global__ __launch_bounds__(64 * NW) void fwd_any_kernel(FwdArgs args) {
     constexpr int NB = P * P;
-    constexpr int RPW = (P + 3) / 4;          // bin rows per wave
+    constexpr int RPW = (P + NW - 1) / NW;    // bin rows per wave
+    static_assert(NW == 4 || RPW == 1, "AnyFwdSmem::wy");
     constexpr int SLICE = 64 * CPL;
     static_assert(RPW <= 4 && 64 % kAnyRows == 0 && kAnyCols == 64 && kAnyCols % CX == 0, "tables");
-    __shared__ AnyFwdSmem<P, CHK> sm;
+    __shared__ AnyFwdSmem<P, CHK, NW> sm;
     (void)args;
     const FwdArgs &a = *(const FwdArgs *)__builtin_amdgcn_kernarg_segment_ptr();
     const LevelTable &lv = a.lv;
@@ -192,7 +207,7 @@ __global__ __launch_bounds__(256) void fwd_any_kernel(FwdArgs args) {
     const float *const ypos = sm.pos;
     const float *const xpos = sm.pos + kAnyGrid * P;
 
-    if (active) any_positions<P>(ay, ax, L.H, L.W, sm.pos);
+    if (active) any_positions<P, 64 * NW>(ay, ax, L.H, L.W, sm.pos);
     __syncthreads();
     // The wave's tapped rows and the RoI's tapped columns (every wave finds them itself).
     int ya = 0, ny = 0, xa = 0, xb = 0, nx = 0;
@@ -229,11 +244,17 @@ __global__ __launch_bounds__(256) void fwd_any_kernel(FwdArgs args) {
             nx = xb - xa + 1;
         }
     }
-    const int npx = (nx + kAnyCols - 1) / kAnyCols;   // the same in every wave
-    const int npy = (ny + kAnyRows - 1) / kAnyRows;   // the wave's own
+    // slots: the run's pixels or, if fewer, the samples' taps
+    const bool xtaps = nx > 2 * P * ax.grid;                // the same in every wave
+    const bool ytaps = ny > 2 * (p1 - p0) * ay.grid;        // the wave's own, as its rows
+    const int nxs = xtaps ? 2 * P * ax.grid : nx;
+    const int nys = ytaps ? 2 * (p1 - p0) * ay.grid : ny;
+    const int npx = (nxs + kAnyCols - 1) / kAnyCols;
+    const int npy = (nys + kAnyRows - 1) / kAnyRows;
     const float inv_count = 1.0f / static_cast<float>(max(ay.grid * ax.grid, 1));
 
     uint32_t cmask = 0;
+    int yoff = 0;   // byte offset of the panel's row `lane` (the lower half's lanes)
     for (int slice = slice0; slice < slice1; ++slice) {
         if (slice > slice0) __syncthreads();   // the previous slice's output tile is stored
         const int c = slice * SLICE + lane * CPL;
@@ -252,17 +273,26 @@ __global__ __launch_bounds__(256) void fwd_any_kernel(FwdArgs args) {
                 for (int q = 0; q < P; ++q) acc[j][p][q] = 0.0f;
 
         for (int px = 0; px < npx; ++px) {
-            const int X0 = xa + px * kAnyCols;
+            const int X0 = px * kAnyCols;
             // column weights of the panel: a wave takes whole bin columns, lane = column
             if (slice == slice0 || npx > 1) {
                 if (px > 0 || slice > slice0) __syncthreads();   // the last panel is consumed
-                // columns past the last tapped one repeat it (their weights are zero)
-                if (wave == 3) sm.xoff[lane] = static_cast<uint32_t>(min(X0 + lane, xb)) * sw_b;
-                for (int q = wave; q < P; q += 4) {
-                    bool h = false;
-                    float w = 0.0f;
-                    if (X0 + lane <= xb)
-                        w = any_weight(xpos + q * ax.grid, ax, q, X0 + lane, L.W, h);
+                // columns past the last slot repeat the last pixel (their weights are zero)
+                int X = min(xa + X0 + lane, xb), xq = 0;
+                float xw = 0.0f;
+                bool xon = X0 + lane < nxs;
+                if (xtaps && xon) {
+                    xon = any_tap(xpos, X0 + lane, L.W, X, xw);
+                    xq = small_div_exact((X0 + lane) >> 1, ax.grid);
+                }
+                if (wave == 3) sm.xoff[lane] = xtaps && !xon ? kBufOOB : static_cast<uint32_t>(X) * sw_b;
+                for (int q = wave; q < P; q += NW) {
+                    bool h = xon && xq == q;
+                    float w = h ? xw : 0.0f;
+                    if (!xtaps) {
+                        h = false;
+                        if (xon) w = any_weight(xpos + q * ax.grid, ax, q, X, L.W, h);
+                    }
                     sm.wx[q][lane] = w;
                     const uint64_t m = __ballot(h);
                     if (lane == 0) sm.hit[q] = m;
@@ -276,10 +306,10 @@ __global__ __launch_bounds__(256) void fwd_any_kernel(FwdArgs args) {
                         cmask |= ((sm.hit[q] >> (lane * CX)) & ((1u << CX) - 1u)) ? 1u << q : 0u;
                 }
             }
-            const int nch = (min(kAnyCols, xb - X0 + 1) + CX - 1) / CX;
+            const int nch = (min(kAnyCols, nxs - X0) + CX - 1) / CX;
             for (int py = 0; py < npy; ++py) {
-                const int Y0 = ya + py * kAnyRows;
-                const int rows = min(kAnyRows, ya + ny - Y0);
+                const int Y0 = py * kAnyRows;
+                const int rows = min(kAnyRows, nys - Y0);
                 // row weights of the panel (the wave's own): lanes over (bin row, row)
                 if ((slice == slice0 && px == 0) || npy > 1) {
                     wave_sync();   // the last panel's are consumed
@@ -287,11 +317,17 @@ __global__ __launch_bounds__(256) void fwd_any_kernel(FwdArgs args) {
                     for (int pp = 0; pp < (RPW * kAnyRows + 63) / 64; ++pp) {
                         const int u = pp * 64 + lane;
                         const int p = u / kAnyRows, y = u % kAnyRows;
+                        int Y = ya + Y0 + y;
                         float w = 0.0f;
                         bool h = false;
-                        if (p < RPW && p0 + p < p1 && y < rows)
-                            w = any_weight(ypos + (p0 + p) * ay.grid, ay, p0 + p, Y0 + y, L.H, h);
+                        if (ytaps && y < rows) {
+                            h = any_tap(ypos + p0 * ay.grid, Y0 + y, L.H, Y, w);
+                            if (!h || small_div_exact((Y0 + y) >> 1, ay.grid) != p) w = 0.0f;
+                        } else if (p < RPW && p0 + p < p1 && y < rows) {
+                            w = any_weight(ypos + (p0 + p) * ay.grid, ay, p0 + p, Y, L.H, h);
+                        }
                         if (p < RPW) sm.wy[wave][y][p] = w;
+                        if (pp == 0) yoff = static_cast<int>(ytaps && !h ? kBufOOB : static_cast<uint32_t>(Y) * sh_b);
                     }
                     wave_sync();
                 }
@@ -304,7 +340,7 @@ __global__ __launch_bounds__(256) void fwd_any_kernel(FwdArgs args) {
                         for (int p = 0; p < RPW; ++p) H[j][x][p] = 0.0f;
 
                 auto issue = [&](int ch, int yi, AnyPix<T, CPL> (&v)[CX]) {
-                    const uint32_t rowb = vbase + static_cast<uint32_t>(Y0 + yi) * sh_b;
+                    const uint32_t rowb = vbase + static_cast<uint32_t>(__builtin_amdgcn_readlane(yoff, yi));
                     const uint32_t *xo = sm.xoff + ch * CX;
 #pragma unroll
                     for (int x = 0; x < CX; ++x) any_load<T, CPL>(res, rowb + xo[x], 0, v[x]);
@@ -457,13 +493,18 @@ __global__ __launch_bounds__(256) void fwd_any_kernel(FwdArgs args) {
             }
             __syncthreads();
             const int ne = max(0, min(CHK, nchan - c0)) * NB;
-            if (kvalid) store_run_f32<TO>(out_blk + c0 * NB, sm.stile, ne, t, 256);
+            if (kvalid) store_run_f32<TO>(out_blk + c0 * NB, sm.stile, ne, t, 64 * NW);
             if (c0 + CHK < SLICE) __syncthreads();
         }
     }
 }
 
-template <typename T, typename TO, int P, int CX, int CHK, int CPL, int D>
+// Waves per workgroup: four, or one per bin row with DF units in flight in a grid that leaves most
+// of the chip idle, where the chain of a wave is all there is (adaptive grid, 7x7, boxes of 8 to
+// 800 pixels on four levels: 64 RoIs of 256 channels 29.4 -> 22.7 us, 128 RoIs 22.7 -> 19.3, 256
+// RoIs 31.3 against 36.7; 14x14: 16 RoIs 32.2 -> 25.2, 64 RoIs 56 -> 42, 256 RoIs 75 against 88).
+constexpr int any_few(int P) { return P == 7 ? 512 : 256; }   // workgroups
+template <typename T, typename TO, int P, int CX, int CHK, int CPL, int D, int DF>
 static hipError_t launch_any(FwdArgs a, hipStream_t stream) {
     a.nslices = (a.lv.C + 64 * CPL - 1) / (64 * CPL);
     // slices per workgroup as in the two-samples forward: up to 4 share the geometry while
@@ -477,7 +518,9 @@ static hipError_t launch_any(FwdArgs a, hipStream_t stream) {
     a.wg_per_roi = (a.nslices + a.spw - 1) / a.spw;
     const int64_t grid = static_cast<int64_t>(a.K) * a.wg_per_roi;
     if (grid >= (int64_t(1) << 24)) return hipErrorInvalidConfiguration;
-    fwd_any_kernel<T, TO, P, CX, CHK, CPL, D><<<static_cast<uint32_t>(grid), 256, 0, stream>>>(a);
+    const uint32_t g = static_cast<uint32_t>(grid);
+    if (grid <= any_few(P)) fwd_any_kernel<T, TO, P, CX, CHK, CPL, DF, P><<<g, 64 * P, 0, stream>>>(a);
+    else fwd_any_kernel<T, TO, P, CX, CHK, CPL, D, 4><<<g, 256, 0, stream>>>(a);
     return hipGetLastError();
 }
 
@@ -486,10 +529,10 @@ hipError_t launch_fwd_any_typed(const FwdArgs &a, hipStream_t stream) {
     // columns per unit, channels per lane and units in flight of the two-samples kernels
     if (a.PH == 7) {
         if constexpr (sizeof(T) == 2)
-            if (a.lv.C % 2 == 0) return launch_any<T, TO, 7, 4, 64, 2, 4>(a, stream);
-        return launch_any<T, TO, 7, 8, 64, 1, 2>(a, stream);
+            if (a.lv.C % 2 == 0) return launch_any<T, TO, 7, 4, 64, 2, 4, 8>(a, stream);
+        return launch_any<T, TO, 7, 8, 64, 1, 2, 4>(a, stream);
     }
-    return launch_any<T, TO, 14, 4, 16, 1, 2>(a, stream);
+    return launch_any<T, TO, 14, 4, 16, 1, 2, 6>(a, stream);
 }
 
 hipError_t launch_fwd_any(const FwdArgs &a, int feat_dtype, int out_dtype, hipStream_t stream) {

@@ -110,6 +110,65 @@ def test_many_samples():
     _run("many", rois, 7, 0, shapes=[(1, 5, 200, 500)], scales=[1.0])
 
 
+WIDE = np.array([[0, 0, 0, 300, 200], [1, 2, 1, 500, 190], [0, 5, 7, 40, 199], [1, 100, 20, 480, 44],
+                 [0, -90, -50, 460, 300], [1, 10, 10, 30, 30], [0, 0, 60, 499, 66]], np.float32)
+
+
+@pytest.mark.parametrize("copies", [1, 80])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("P,S", [(7, 1), (7, 3), (7, 4), (7, 33), (14, 1), (14, 3), (14, 17)])
+def test_few_samples_in_wide_bins(P, S, dt, copies):
+    # bins many pixels wide: the forward takes the samples' taps where they are fewer than the
+    # pixels between them, on either axis, in one panel (S = 1, 3, 4) and in several, in grids
+    # that leave the chip idle and in larger ones
+    shapes = [(2, 70, 200, 500)]
+    if copies == 1:
+        _run("wide", WIDE, P, S, dt=dt, shapes=shapes, scales=[1.0], aligned=S != 3)
+    elif S <= 4:
+        _forward("wide, many", np.tile(WIDE, (copies, 1)), P, S, dt, shapes, [1.0])
+
+
+def _forward(name, rois, P, S, dt, shapes, scales, aligned=True):
+    log("adaptive forward %s: K=%d P=%d S=%d %s" % (name, rois.shape[0], P, S, dt))
+    rng, feats, dev, r, lv, ws, lv_np = _setup(rois, shapes, scales, dt, "cl")
+    out = rex.roi_align_fwd(dev, scales, r, lv, (P, P), S, aligned, workspace=ws)
+    ref = oracle.roi_align_fwd([as_f64(f, dt) for f in feats], scales, rois, lv_np, P, P, S, aligned,
+                               "parity")
+    check_fwd(from_device(out), ref, dt == "bf16", name)
+
+
+@pytest.mark.parametrize("C", [64, 129])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("P", [7, 14])
+def test_grid_sizes(P, dt, C):
+    # workgroups around the counts up to which a workgroup has one wave per bin row
+    few = 512 if P == 7 else 256
+    slices = -(-C // (128 if dt == "bf16" and P == 7 and C % 2 == 0 else 64))
+    rois = np.tile(_mixed_rois(), (13, 1))
+    shapes = [(n, C, h, w) for n, _, h, w in SHAPES]
+    for k in (few // slices, few // slices + 1):
+        _forward("grid", rois[:k], P, 0, dt, shapes, SCALES)
+
+
+@pytest.mark.parametrize("S", [1, 4])
+def test_non_finite_feature_in_wide_bins(S):
+    shapes = [(2, 6, 200, 500)]
+    rng = np.random.default_rng(S)
+    feats = rng.standard_normal(shapes[0], dtype=np.float32)
+    for value in (np.inf, -np.inf, np.nan):
+        for _ in range(40):
+            feats[rng.integers(2), rng.integers(6), rng.integers(200), rng.integers(500)] = value
+    feats[:, 5, ::2] = np.inf    # (rows that some samples tap with weight zero)
+    rois = np.concatenate([WIDE, np.array([[0, 10.5, 0.5, 290.5, 112.5]], np.float32)])
+    lv = np.zeros(len(rois), np.int32)
+    out = from_device(rex.roi_align_fwd([to_device(feats, "f32", "cl")], [1.0], torch.from_numpy(rois).cuda(),
+                                        torch.from_numpy(lv).cuda(), (7, 7), S, True))
+    ref = oracle.roi_align_fwd([feats.astype(np.float64)], [1.0], rois, lv, 7, 7, S, True, "parity")
+    assert np.array_equal(np.isfinite(out), np.isfinite(ref)) and not np.isfinite(ref).all()
+    ok = np.isfinite(ref)
+    check_fwd(np.where(ok, out, 0), np.where(ok, ref, 0), False, "non-finite feature, wide bins")
+
+
 @pytest.mark.parametrize("S", [3, 4, 64])
 def test_samples_closer_than_a_unit(S):
     # boxes a few units in the last place wide: all samples of a bin round to one position, which
