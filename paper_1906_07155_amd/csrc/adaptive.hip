@@ -499,12 +499,13 @@ __global__ __launch_bounds__(64 * NW) void fwd_any_kernel(FwdArgs args) {
     }
 }
 
-// Waves per workgroup: four, or one per bin row with DF units in flight in a grid that leaves most
-// of the chip idle, where the chain of a wave is all there is (adaptive grid, 7x7, boxes of 8 to
-// 800 pixels on four levels: 64 RoIs of 256 channels 29.4 -> 22.7 us, 128 RoIs 22.7 -> 19.3, 256
-// RoIs 31.3 against 36.7; 14x14: 16 RoIs 32.2 -> 25.2, 64 RoIs 56 -> 42, 256 RoIs 75 against 88).
+// Waves per workgroup: four, or one per bin row with more loads in flight (units of CXF columns,
+// DF of them, all 64 channels stored at once) in a grid that leaves most of the chip idle, where
+// the chain of a wave is all there is (adaptive grid, 7x7, boxes of 8 to 800 pixels on four levels:
+// 64 RoIs of 256 channels 29.4 -> 22.7 us, 128 RoIs 22.7 -> 19.3, 256 RoIs 31.3 against 36.7; 14x14:
+// 16 RoIs 31.7 -> 20.2, 64 RoIs 56 -> 31, 256 RoIs 75 against 88).
 constexpr int any_few(int P) { return P == 7 ? 512 : 256; }   // workgroups
-template <typename T, typename TO, int P, int CX, int CHK, int CPL, int D, int DF>
+template <typename T, typename TO, int P, int CX, int CHK, int CPL, int D, int CXF, int DF>
 static hipError_t launch_any(FwdArgs a, hipStream_t stream) {
     a.nslices = (a.lv.C + 64 * CPL - 1) / (64 * CPL);
     // slices per workgroup as in the two-samples forward: up to 4 share the geometry while
@@ -519,7 +520,7 @@ static hipError_t launch_any(FwdArgs a, hipStream_t stream) {
     const int64_t grid = static_cast<int64_t>(a.K) * a.wg_per_roi;
     if (grid >= (int64_t(1) << 24)) return hipErrorInvalidConfiguration;
     const uint32_t g = static_cast<uint32_t>(grid);
-    if (grid <= any_few(P)) fwd_any_kernel<T, TO, P, CX, CHK, CPL, DF, P><<<g, 64 * P, 0, stream>>>(a);
+    if (grid <= any_few(P)) fwd_any_kernel<T, TO, P, CXF, 64, CPL, DF, P><<<g, 64 * P, 0, stream>>>(a);
     else fwd_any_kernel<T, TO, P, CX, CHK, CPL, D, 4><<<g, 256, 0, stream>>>(a);
     return hipGetLastError();
 }
@@ -529,10 +530,10 @@ hipError_t launch_fwd_any_typed(const FwdArgs &a, hipStream_t stream) {
     // columns per unit, channels per lane and units in flight of the two-samples kernels
     if (a.PH == 7) {
         if constexpr (sizeof(T) == 2)
-            if (a.lv.C % 2 == 0) return launch_any<T, TO, 7, 4, 64, 2, 4, 8>(a, stream);
-        return launch_any<T, TO, 7, 8, 64, 1, 2, 4>(a, stream);
+            if (a.lv.C % 2 == 0) return launch_any<T, TO, 7, 4, 64, 2, 4, 4, 8>(a, stream);
+        return launch_any<T, TO, 7, 8, 64, 1, 2, 8, 4>(a, stream);
     }
-    return launch_any<T, TO, 14, 4, 16, 1, 2, 6>(a, stream);
+    return launch_any<T, TO, 14, 4, 16, 1, 2, 8, 3>(a, stream);
 }
 
 hipError_t launch_fwd_any(const FwdArgs &a, int feat_dtype, int out_dtype, hipStream_t stream) {
