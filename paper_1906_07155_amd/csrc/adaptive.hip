@@ -530,7 +530,7 @@ hipError_t launch_fwd_any_typed(const FwdArgs &a, hipStream_t stream) {
     // columns per unit, channels per lane and units in flight of the two-samples kernels
     if (a.PH == 7) {
         if constexpr (sizeof(T) == 2)
-            if (a.lv.C % 2 == 0) return launch_any<T, TO, 7, 4, 64, 2, 4, 4, 8>(a, stream);
+            if (channel_pairs(a.lv)) return launch_any<T, TO, 7, 4, 64, 2, 4, 4, 8>(a, stream);
         return launch_any<T, TO, 7, 8, 64, 1, 2, 8, 4>(a, stream);
     }
     return launch_any<T, TO, 14, 4, 16, 1, 2, 8, 3>(a, stream);

@@ -642,7 +642,7 @@ static hipError_t launch_fwd_typed(FwdArgs a, bool fast, hipStream_t stream) {
     if (fast) {
         if (a.PH == 7) {
             // bf16 features: two adjacent channels per lane (one 32-bit load per pixel)
-            // when the channel count is even -- half the load and address instructions of
+            // when the channels pair up -- half the load and address instructions of
             // one channel per lane, and twice the bytes in flight per load (batch-1
             // inference, 1000 RoIs: 49.3 -> 41.9 us; batch 16: 316 -> 268 us).  For
             // binary32 (64-bit loads) the same layout is slower (1024 RoIs: 51.0 -> 54.6
@@ -653,7 +653,7 @@ static hipError_t launch_fwd_typed(FwdArgs a, bool fast, hipStream_t stream) {
             // 16, 8192 RoIs: 241 -> 227 us; batch 1, 1000 RoIs: 38.2 -> 38.0 us); one
             // channel per lane keeps 8 columns and 2 units (1024 RoIs: 47.2 vs 49.0 us).
             if constexpr (sizeof(T) == 2)
-                if (a.lv.C % 2 == 0)
+                if (channel_pairs(a.lv))
                     return launch_fwd_cl<T, TO, 7, 7, REX_FWD_CX2_BF16, 64, 2, REX_FWD_DEPTH2_BF16>(
                         a, stream);
             return launch_fwd_cl<T, TO, 7, 7, kFwdCX, 64, 1>(a, stream);
@@ -966,7 +966,7 @@ __global__ __launch_bounds__(256, 4) void fwd_multi_kernel(FwdMultiArgs m) {
 #ifndef REX_FWD_MULTI_ORDER
 #define REX_FWD_MULTI_ORDER 1
 #endif
-// One channel per lane (fp32 features, or an odd channel count): the 7x7 body needs 78
+// One channel per lane (fp32 features, or channels that do not pair up): the 7x7 body needs 78
 // registers and the 14x14 one 124, so a kernel holding both runs the 7x7 heads at four
 // workgroups per CU instead of six; there the two grids go in two launches, 14x14 first
 // (batch 2, box 1024 + mask 256 RoIs, fp32: 100 us, against 145 in one mixed launch
@@ -980,7 +980,7 @@ __global__ __launch_bounds__(256, 4) void fwd_multi_kernel(FwdMultiArgs m) {
 template <typename T, typename TO>
 static hipError_t launch_fwd_multi_typed(FwdMultiArgs m, hipStream_t stream) {
     // two bf16 channels per lane on the 7x7 grid, as in the single-head launch
-    const int cpl7 = (sizeof(T) == 2 && m.lv.C % 2 == 0) ? 2 : 1;
+    const int cpl7 = (sizeof(T) == 2 && channel_pairs(m.lv)) ? 2 : 1;
     if (REX_FWD_MULTI_ORDER) {
         // 14x14 heads first: their workgroups are the longest, and the short 7x7 ones
         // then fill the tail of the grid

@@ -409,6 +409,20 @@ void plan_bands(PlanArgs &a);   // fills nbands, ndiff, band_base, band_rows, db
 // The output grids of the specialised RoIAlign kernels.
 inline bool fixed_grid(int PH, int PW) { return PH == PW && (PH == 7 || PH == 14); }
 
+// Two adjacent bf16 channels of a channels-last pixel can be read as one aligned 32-bit value:
+// an even channel count, and every pixel of every level at a multiple of 4 bytes (a view may
+// start at an odd element or have odd strides; it is read one channel at a time).
+inline bool channel_pairs(const LevelTable &t) {
+    if (t.C % 2 != 0) return false;
+    for (int l = 0; l < t.num; ++l) {
+        const LevelArg &v = t.l[l];
+        if (reinterpret_cast<uintptr_t>(v.data) % 4 != 0) return false;
+        if ((t.N > 1 && v.sn % 2 != 0) || (v.H > 1 && v.sh % 2 != 0) || (v.W > 1 && v.sw % 2 != 0))
+            return false;
+    }
+    return true;
+}
+
 // Forward: `fast` selects the channels-last kernels (every level stride_c == 1 and a
 // fixed_grid; two samples per axis or, in adaptive.hip, any number); otherwise the NCHW or
 // the general strided kernel.  fwd_fast_available: the two-samples kernels' set.

@@ -427,3 +427,40 @@ def test_non_finite_features(out_hw):
     assert np.array_equal(np.isneginf(got), np.isneginf(ref))
     fin = np.isfinite(ref)
     check_fwd(np.where(fin, got, 0.0), np.where(fin, ref, 0.0), False, "non-finite features")
+
+
+def _odd_views(arrs):
+    """bf16 channels-last views whose pixels do not lie at multiples of 4 bytes: one starting at an
+    odd element (even strides), one with an odd pixel stride, in turn over the levels."""
+    out = []
+    for i, a in enumerate(arrs):
+        n, c, h, w = a.shape
+        pad = 2 if i % 2 == 0 else 1
+        big = torch.empty((n, h, w, c + pad), dtype=torch.bfloat16, device="cuda")
+        big.fill_(float("nan"))
+        v = (big[..., 1:c + 1] if pad == 2 else big[..., :c]).permute(0, 3, 1, 2)
+        v.copy_(to_device(a, "bf16", "nchw"))
+        assert v.stride(1) == 1 and (v.data_ptr() % 4 != 0 or v.stride(3) % 2 == 1)
+        out.append(v)
+    return out
+
+
+@pytest.mark.parametrize("S", [2, 0, 1])
+@pytest.mark.parametrize("P", [7, 14])
+def test_bf16_views_off_a_word(P, S):
+    # an even channel count, but no aligned pairs of channels: same result, one head and several
+    rng = np.random.default_rng(P)
+    shapes, scales = [(2, 70, 25, 90), (2, 70, 13, 45)], [0.25, 0.125]
+    feats = [W.f32_to_bf16_bits(rng.standard_normal(s, dtype=np.float32)) for s in shapes]
+    rois = W.draw_rois(rng, 2, 24, (100, 360), (1.0, 300.0))
+    r = torch.from_numpy(rois).cuda()
+    views = _odd_views(feats)
+    lv, ws = rex.plan(views, scales, r, 56.0)
+    lv_np = oracle.level_map(rois, 2, 56.0)
+    ref = oracle.roi_align_fwd([as_f64(f, "bf16") for f in feats], scales, rois, lv_np, P, P, S, True,
+                               "parity")
+    out = rex.roi_align_fwd(views, scales, r, lv, (P, P), S, True, workspace=ws)
+    check_fwd(from_device(out), ref, True, "views off a word")
+    heads = [dict(rois=r, roi_levels=lv, out_size=(p, p), sampling_ratio=S, workspace=ws) for p in (7, 14)]
+    multi = rex.roi_align_fwd_multi(views, scales, heads)
+    assert torch.equal(multi[P == 14], out)
