@@ -281,19 +281,19 @@ __global__ __launch_bounds__(256) void bwd_cl_kernel(BwdArgs a) {
 // and the contribution is  acc[r][q] += sum_ph Wy[ph][r] * sum_pw Wx[pw][q] * g[ph][pw].
 
 // LDS of one head's pass over a tile (see gather_phase).
-template <typename TG, int PH, int PW, int S>
+template <typename TG, int PH, int PW, int S, bool FEW>
 struct GatherSmem {
     static constexpr int NR = PH * S;
     static constexpr int NCOL = PW * S;
     static constexpr int T = 8;
     static constexpr int NB = PH * PW;
     // Bin rows staged at a time: all of them, except for binary32 14x14, whose 50 KiB block
-    // held the kernel to two workgroups per CU (mask head batch 2 step 136 us, 122-132 in parts;
-    // box and mask heads of batch 2 307 -> 252 us): an item of the walk is then one part of
+    // holds the kernel to two workgroups per CU (two images of 800 x 1344, 256 RoIs, the backward:
+    // 88 us, 69 in parts; with the box head 197 -> 159): an item of the walk is then one part of
     // a RoI, 8 or 6 bin rows, with its own tap extent (part 1 starts 448 bytes into a
     // channel's 784, on 16 bytes as every channel does).  A channel's part takes PITCH
-    // elements of the slot.
-    static constexpr int RP = sizeof(TG) == 4 && PH == 14 ? 8 : PH;
+    // elements of the slot.  FEW: the form for few workgroups (gather_few).
+    static constexpr int RP = sizeof(TG) == 4 && PH == 14 && !FEW ? 8 : PH;
     static constexpr int NPART = (PH + RP - 1) / RP;
     static constexpr int PITCH = NPART == 1 ? NB : RP * PW + 4;
     static constexpr int ITEMS = 64 * NPART;
@@ -310,8 +310,9 @@ struct GatherSmem {
     // The staged gradient blocks form a ring of NBUF: the next RoI's block is copied
     // into the other slot by the buffer unit while the current one is consumed, when
     // two blocks fit in 28 KiB.  Four workgroups per CU beat a second slot: the 25 KiB
-    // blocks of bf16 14x14 take one (batch-16 mask head step: two slots 849 us, one 633).
-    static constexpr int NBUF = 2 * GBP * 4 <= 28 * 1024 ? 2 : 1;
+    // blocks of bf16 14x14 take one (batch-16 mask head step: two slots 849 us, one 633),
+    // in few workgroups two.
+    static constexpr int NBUF = 2 * GBP * 4 <= (FEW ? 56 : 28) * 1024 ? 2 : 1;
     using Elem = std::conditional_t<sizeof(TG) == 4, uint32_t, uint16_t>;
     Tap tap[2][NR + NCOL];
     __align__(16) float wy[4][RP * T];
@@ -324,20 +325,20 @@ struct GatherSmem {
 
 // One staged gradient block.  The ring's slots are separate LDS variables, so the
 // compiler can tell that reading one slot does not depend on the copy into the other.
-template <typename TG, int PH, int PW, int S>
+template <typename TG, int PH, int PW, int S, bool FEW>
 struct GatherBlock {
-    __align__(16) uint32_t g[GatherSmem<TG, PH, PW, S>::GBP];
+    __align__(16) uint32_t g[GatherSmem<TG, PH, PW, S, FEW>::GBP];
 };
 
 // One head's RoIs binned to tile t, added into this wave's quadrant accumulators:
 //   acc[r][q] += sum over RoIs, bins: Wy[ph][r] * sum_pw Wx[pw][q] * g[ph][pw].
 // Every wave of the workgroup calls it (it holds workgroup barriers).
-template <typename TG, int PH, int PW, int S>
+template <typename TG, int PH, int PW, int S, bool FEW>
 __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTable &lv, int t,
                                              const GatherTile &x, float (&acc)[8][8],
-                                             GatherSmem<TG, PH, PW, S> &sm, uint32_t *slot0,
+                                             GatherSmem<TG, PH, PW, S, FEW> &sm, uint32_t *slot0,
                                              uint32_t *slot1) {
-    using SM = GatherSmem<TG, PH, PW, S>;
+    using SM = GatherSmem<TG, PH, PW, S, FEW>;
     constexpr int NR = SM::NR, NCOL = SM::NCOL, T = SM::T, NB = SM::NB, GB = SM::GB;
     constexpr int NBUF = SM::NBUF;
     constexpr int RP = SM::RP, NPART = SM::NPART;
@@ -458,8 +459,9 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
         const typename SM::Elem *gsrc = reinterpret_cast<const typename SM::Elem *>(gblk);
         const int ymin = sm.rng[j][0], ymax = sm.rng[j][1];
         const int xmin = sm.rng[j][2], xmax = sm.rng[j][3];
+        const int item = sm.k[j];
         if (!x.wave_on || ymax < R0 || ymin >= R0 + T || xmax < Q0 || xmin >= Q0 + T) return;
-        const int ph0 = NPART == 1 ? 0 : (uniform_i(sm.k[j]) % NPART) * RP;   // the part's first bin row
+        const int ph0 = NPART == 1 ? 0 : (uniform_i(item) % NPART) * RP;   // the part's first bin row
         // This quadrant's separable weights and which bin rows / columns reach it.
         // Ballot bit p * 64 + i marks a nonzero weight of lane u = p * 64 + i
         // (u = bin * 8 + row or column of the quadrant).
@@ -620,13 +622,14 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
 }
 
 
-// Four workgroups per CU: every instance fits 40 KiB of LDS and, held to it, 128 registers.
-template <typename TG, int PH, int PW, int S>
-__global__ __launch_bounds__(256, 4) void bwd_gather_kernel(GatherArgs a) {
-    __shared__ GatherSmem<TG, PH, PW, S> sm;
-    __shared__ GatherBlock<TG, PH, PW, S> blk0;
-    constexpr bool two = GatherSmem<TG, PH, PW, S>::NBUF == 2;
-    __shared__ GatherBlock<TG, two ? PH : 1, two ? PW : 1, S> blk1;
+// Four workgroups per CU (FEW: two): every instance fits 40 KiB of LDS and, held to it, 128
+// registers.
+template <typename TG, int PH, int PW, int S, bool FEW>
+__global__ __launch_bounds__(256, FEW ? 2 : 4) void bwd_gather_kernel(GatherArgs a) {
+    __shared__ GatherSmem<TG, PH, PW, S, FEW> sm;
+    __shared__ GatherBlock<TG, PH, PW, S, FEW> blk0;
+    constexpr bool two = GatherSmem<TG, PH, PW, S, FEW>::NBUF == 2;
+    __shared__ GatherBlock<TG, two ? PH : 1, two ? PW : 1, S, FEW> blk1;
     GatherTile x;
     const int t = gather_tile(a, a.tile_order, x);
     float acc[8][8];
@@ -634,9 +637,9 @@ __global__ __launch_bounds__(256, 4) void bwd_gather_kernel(GatherArgs a) {
     for (int r = 0; r < 8; ++r)
 #pragma unroll
         for (int q = 0; q < 8; ++q) acc[r][q] = 0.0f;
-    gather_phase<TG, PH, PW, S>(a.head[0], a.lv, t, x, acc, sm, blk0.g,
-                                two ? blk1.g : nullptr);
-    static_assert(GatherSmem<TG, PH, PW, S>::GBP >= 4 * 512, "store scratch in the first slot");
+    gather_phase<TG, PH, PW, S, FEW>(a.head[0], a.lv, t, x, acc, sm, blk0.g,
+                                   two ? blk1.g : nullptr);
+    static_assert(GatherSmem<TG, PH, PW, S, FEW>::GBP >= 4 * 512, "store scratch in the first slot");
     __syncthreads();   // the staging slots are free: every wave has consumed its last RoI
     gather_store(x, a.zero_init, acc,
                  reinterpret_cast<float *>(blk0.g) + (threadIdx.x >> 6) * 512);
@@ -646,10 +649,10 @@ __global__ __launch_bounds__(256, 4) void bwd_gather_kernel(GatherArgs a) {
 // R-CNN step): the workgroup walks head 0's RoIs of its tile, then head 1's, into the
 // same accumulators, and writes every gradient element once.  Tiles follow head 0's
 // order.
-template <typename TG, int PH0, int PW0, int PH1, int PW1>
-__global__ __launch_bounds__(256, 4) void bwd_gather2_kernel(GatherArgs a) {
-    using SM0 = GatherSmem<TG, PH0, PW0, 2>;
-    using SM1 = GatherSmem<TG, PH1, PW1, 2>;
+template <typename TG, int PH0, int PW0, int PH1, int PW1, bool FEW>
+__global__ __launch_bounds__(256, FEW ? 2 : 4) void bwd_gather2_kernel(GatherArgs a) {
+    using SM0 = GatherSmem<TG, PH0, PW0, 2, FEW>;
+    using SM1 = GatherSmem<TG, PH1, PW1, 2, FEW>;
     union Smem {
         SM0 h0;
         SM1 h1;
@@ -665,10 +668,10 @@ __global__ __launch_bounds__(256, 4) void bwd_gather2_kernel(GatherArgs a) {
     for (int r = 0; r < 8; ++r)
 #pragma unroll
         for (int q = 0; q < 8; ++q) acc[r][q] = 0.0f;
-    gather_phase<TG, PH0, PW0, 2>(a.head[0], a.lv, t, x, acc, sm.h0, stage,
+    gather_phase<TG, PH0, PW0, 2, FEW>(a.head[0], a.lv, t, x, acc, sm.h0, stage,
                                   SM0::NBUF == 2 ? stage + SM0::GBP : nullptr);
     __syncthreads();   // head 0's LDS is no longer read
-    gather_phase<TG, PH1, PW1, 2>(a.head[1], a.lv, t, x, acc, sm.h1, stage,
+    gather_phase<TG, PH1, PW1, 2, FEW>(a.head[1], a.lv, t, x, acc, sm.h1, stage,
                                   SM1::NBUF == 2 ? stage + SM1::GBP : nullptr);
     static_assert(kStage0 >= 4 * 512 && kStage1 >= 4 * 512, "store scratch in the ring");
     __syncthreads();   // the staging ring is free
@@ -680,17 +683,38 @@ bool gather_available(int PH, int PW, int S) {
     return S == 2 && ((PH == 7 && PW == 7) || (PH == 14 && PW == 14));
 }
 
-template <typename TG>
-static void launch_gather2_typed(const GatherArgs &a, uint32_t g, hipStream_t stream) {
+template <typename TG, bool FEW>
+static void launch_gather_form(const GatherArgs &a, uint32_t g, hipStream_t stream) {
     const bool b0 = a.PH == 7, b1 = a.head[1].PH == 7;
+    if (a.nheads == 1) {
+        if (b0) bwd_gather_kernel<TG, 7, 7, 2, false><<<g, 256, 0, stream>>>(a);
+        else bwd_gather_kernel<TG, 14, 14, 2, FEW><<<g, 256, 0, stream>>>(a);
+        return;
+    }
+    constexpr bool few = FEW && sizeof(TG) == 4;   // (gather_few)
     if (b0 && b1)
-        bwd_gather2_kernel<TG, 7, 7, 7, 7><<<g, 256, 0, stream>>>(a);
+        bwd_gather2_kernel<TG, 7, 7, 7, 7, false><<<g, 256, 0, stream>>>(a);
     else if (b0)
-        bwd_gather2_kernel<TG, 7, 7, 14, 14><<<g, 256, 0, stream>>>(a);
+        bwd_gather2_kernel<TG, 7, 7, 14, 14, few><<<g, 256, 0, stream>>>(a);
     else if (b1)
-        bwd_gather2_kernel<TG, 14, 14, 7, 7><<<g, 256, 0, stream>>>(a);
+        bwd_gather2_kernel<TG, 14, 14, 7, 7, few><<<g, 256, 0, stream>>>(a);
     else
-        bwd_gather2_kernel<TG, 14, 14, 14, 14><<<g, 256, 0, stream>>>(a);
+        bwd_gather2_kernel<TG, 14, 14, 14, 14, few><<<g, 256, 0, stream>>>(a);
+}
+
+// A 14x14 grid in few workgroups: the time is the longest tile's chain of RoIs and not the chip's
+// throughput, and two workgroups per CU with whole blocks (binary32) or two slots (bf16) beat four.
+// The long chains are as many as images and channel groups; where these are many, or the RoIs of
+// each, four per CU are faster on few workgroups too.  (Two per CU against four, 256 binary32
+// channels, RoIs per image: 800 x 1344, one image, 128: 47 / 55 us, two images 88 / 69; 400 x 672,
+// 128: one image 78 / 106, two 80 / 107, three 94 / 109, four 125 / 110; 32: four 48 / 52; 512: three
+// 310 / 301.  bf16, 400 x 672: one image 73 / 76, two 74 / 78; three 87 / 79.  Box and mask head: one
+// 800 x 1344 image 107 / 95, one 400 x 672 image 148 / 161, bf16 no gain.)
+static bool gather_few(const GatherArgs &a, int gout_dtype, int64_t grid) {
+    if (gout_dtype == kBF16) return a.nheads == 1 && grid <= 1024;
+    if (a.nheads == 2) return grid <= 1024;
+    return grid <= 2304 && (static_cast<int64_t>(a.lv.N) * a.ncg <= 8 ||
+                            static_cast<int64_t>(a.head[0].K) * a.ncg <= 1536);
 }
 
 hipError_t launch_gather(GatherArgs a, int gout_dtype, hipStream_t stream) {
@@ -700,25 +724,15 @@ hipError_t launch_gather(GatherArgs a, int gout_dtype, hipStream_t stream) {
     if (grid >= (int64_t(1) << 24)) return hipErrorInvalidConfiguration;
     const uint32_t g = static_cast<uint32_t>(grid);
     if (a.S != 2) return launch_gather_any(a, g, gout_dtype, stream);
-    if (a.nheads == 2) {
-        // both heads' gradients have one dtype here (the host checks it)
-        if (gout_dtype == kF32)
-            launch_gather2_typed<float>(a, g, stream);
-        else
-            launch_gather2_typed<uint16_t>(a, g, stream);
+    const bool few = gather_few(a, gout_dtype, grid);
+    // both heads' gradients have one dtype here (the host checks it)
+    if (gout_dtype == kF32) {
+        if (few) launch_gather_form<float, true>(a, g, stream);
+        else launch_gather_form<float, false>(a, g, stream);
         return hipGetLastError();
     }
-    if (gout_dtype == kF32) {
-        if (a.PH == 7)
-            bwd_gather_kernel<float, 7, 7, 2><<<g, 256, 0, stream>>>(a);
-        else
-            bwd_gather_kernel<float, 14, 14, 2><<<g, 256, 0, stream>>>(a);
-    } else {
-        if (a.PH == 7)
-            bwd_gather_kernel<uint16_t, 7, 7, 2><<<g, 256, 0, stream>>>(a);
-        else
-            bwd_gather_kernel<uint16_t, 14, 14, 2><<<g, 256, 0, stream>>>(a);
-    }
+    if (few) launch_gather_form<uint16_t, true>(a, g, stream);
+    else launch_gather_form<uint16_t, false>(a, g, stream);
     return hipGetLastError();
 }
 
