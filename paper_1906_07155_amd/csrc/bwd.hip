@@ -333,7 +333,7 @@ struct GatherBlock {
 // One head's RoIs binned to tile t, added into this wave's quadrant accumulators:
 //   acc[r][q] += sum over RoIs, bins: Wy[ph][r] * sum_pw Wx[pw][q] * g[ph][pw].
 // Every wave of the workgroup calls it (it holds workgroup barriers).
-template <typename TG, int PH, int PW, int S, bool FEW>
+template <typename TG, int PH, int PW, int S, bool FEW, bool ANY>
 __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTable &lv, int t,
                                              const GatherTile &x, float (&acc)[8][8],
                                              GatherSmem<TG, PH, PW, S, FEW> &sm, uint32_t *slot0,
@@ -369,9 +369,17 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
     // zeros past the valid channels.
     const int nvalid = x.nch * NB;
     // 16-byte copies need every block 16-byte aligned: the gradient's base and a RoI's bytes
-    // (a channel group's are a multiple of 16)
-    const bool wide = (kstride * int64_t(sizeof(TG)) & 15) == 0 &&
+    // (a channel group's are a multiple of 16).  ANY: the form for RoIs of bf16 values that are not
+    // (in one kernel with the other, the other has 14 registers more and takes 3 % longer).
+    const bool wide = !(ANY && sizeof(TG) == 2) && (kstride * int64_t(sizeof(TG)) & 15) == 0 &&
                       (reinterpret_cast<uintptr_t>(h.gout) & 15u) == 0;
+    // Element of the slot at which an item's block starts: 1 where a bf16 block starts inside a
+    // word (an odd start of the tensor, an odd RoI after odd RoIs), but for the tensor's first.
+    const int odd_rois = ANY && sizeof(TG) == 2 ? static_cast<int>(kstride & 1) : 0;
+    const int odd_start = ANY && sizeof(TG) == 2 ? static_cast<int>((reinterpret_cast<uintptr_t>(h.gout) >> 1) & 1u) : 0;
+    auto block_shift = [&](int item) {
+        return x.cg == 0 && item == 0 ? 0 : (item & odd_rois) ^ odd_start;
+    };
     auto fetch = [&](int j, uint32_t *gdst) {
         const int item = uniform_i(sm.k[j]);   // one resource for the wave, no waterfall
         const char *src = static_cast<const char *>(h.gout) +
@@ -428,12 +436,44 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 4, off, 0, 0, 0);
                 }
             }
-        } else {
-            // (a 16-bit copy to LDS fills a 32-bit slot, so packed values go through registers)
+        } else if constexpr (!ANY) {
+            // bf16, a gradient that does not start on 16 bytes: through registers
             uint16_t *const g16 = reinterpret_cast<uint16_t *>(gdst);
 #pragma unroll 4
             for (int e = tid; e < GB; e += 256)
                 g16[e] = static_cast<uint16_t>(buf_load_raw<uint16_t>(rs, static_cast<uint32_t>(e) * 2u));
+        } else {
+            // bf16 blocks not 16-byte aligned: 4 bytes per lane and instruction, from the word
+            // that holds the block's first value on, which is then the slot's element block_shift
+            // (a 16-bit copy to LDS would fill a 32-bit slot), to the word that holds its last.
+            // Where the tensor itself starts or ends inside a word, its first or last block goes
+            // through registers: nothing outside the tensor is read.
+            const int shift = block_shift(item);
+            const bool first = (reinterpret_cast<uintptr_t>(src) & 2u) != 0 && shift == 0;
+            const bool last = item == h.K - 1 && x.cg == (lv.C - 1) / 64 && ((nvalid + shift) & 1) != 0;
+            if (first || last) {
+                uint16_t *const g16 = reinterpret_cast<uint16_t *>(gdst) + shift;
+#pragma unroll 1
+                for (int e = tid; e < GB; e += 256)
+                    g16[e] = static_cast<uint16_t>(buf_load_raw<uint16_t>(rs, static_cast<uint32_t>(e) * 2u));
+            } else {
+                const __amdgpu_buffer_rsrc_t rw =
+                    make_rsrc(src - 2 * shift, static_cast<uint32_t>((nvalid + shift + 1) >> 1) * 4u);
+                constexpr int RUNS = (GB / 2 + 1 + 63) / 64;
+                static_assert(RUNS * 64 <= SM::GBP && GB / 2 < SM::GBP, "the slot");
+                auto copy = [&](int run) {
+                    auto *dst = (__attribute__((address_space(3))) void *)(gdst + 64 * run);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, dst, 4, static_cast<uint32_t>(64 * run + lane) * 4u, 0, 0, 0);
+                };
+                if constexpr (NBUF == 2) {
+#pragma unroll
+                    for (int m = 0; m < (RUNS + 3) / 4; ++m)
+                        if (m < RUNS / 4 || wave + 4 * m < RUNS) copy(wave + 4 * m);
+                } else {   // (unrolled: 44 spills)
+#pragma unroll 1
+                    for (int run = wave; run < RUNS; run += 4) copy(run);
+                }
+            }
         }
     };
     // The copies of this wave are complete (vmcnt 0); a barrier then publishes them.
@@ -515,6 +555,7 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
         wave_sync();
 
         const typename SM::Elem *gl = gsrc + lane * SM::PITCH + pwa;   // this lane's channel
+        if constexpr (ANY && sizeof(TG) == 2) gl += block_shift(uniform_i(item));
         const float *wxa = wx + pwa * T;
         gather_rows<TG, PW>(acc, gl, wxa, wy, yb, pha, phb, pwb - pwa + 1);
         // the weights are rewritten for the next RoI only after the next barrier
@@ -624,7 +665,7 @@ __device__ __forceinline__ void gather_phase(const GatherHead &h, const LevelTab
 
 // Four workgroups per CU (FEW: two): every instance fits 40 KiB of LDS and, held to it, 128
 // registers.
-template <typename TG, int PH, int PW, int S, bool FEW>
+template <typename TG, int PH, int PW, int S, bool FEW, bool ANY>
 __global__ __launch_bounds__(256, FEW ? 2 : 4) void bwd_gather_kernel(GatherArgs a) {
     __shared__ GatherSmem<TG, PH, PW, S, FEW> sm;
     __shared__ GatherBlock<TG, PH, PW, S, FEW> blk0;
@@ -637,7 +678,7 @@ __global__ __launch_bounds__(256, FEW ? 2 : 4) void bwd_gather_kernel(GatherArgs
     for (int r = 0; r < 8; ++r)
 #pragma unroll
         for (int q = 0; q < 8; ++q) acc[r][q] = 0.0f;
-    gather_phase<TG, PH, PW, S, FEW>(a.head[0], a.lv, t, x, acc, sm, blk0.g,
+    gather_phase<TG, PH, PW, S, FEW, ANY>(a.head[0], a.lv, t, x, acc, sm, blk0.g,
                                    two ? blk1.g : nullptr);
     static_assert(GatherSmem<TG, PH, PW, S, FEW>::GBP >= 4 * 512, "store scratch in the first slot");
     __syncthreads();   // the staging slots are free: every wave has consumed its last RoI
@@ -649,7 +690,7 @@ __global__ __launch_bounds__(256, FEW ? 2 : 4) void bwd_gather_kernel(GatherArgs
 // R-CNN step): the workgroup walks head 0's RoIs of its tile, then head 1's, into the
 // same accumulators, and writes every gradient element once.  Tiles follow head 0's
 // order.
-template <typename TG, int PH0, int PW0, int PH1, int PW1, bool FEW>
+template <typename TG, int PH0, int PW0, int PH1, int PW1, bool FEW, bool ANY>
 __global__ __launch_bounds__(256, FEW ? 2 : 4) void bwd_gather2_kernel(GatherArgs a) {
     using SM0 = GatherSmem<TG, PH0, PW0, 2, FEW>;
     using SM1 = GatherSmem<TG, PH1, PW1, 2, FEW>;
@@ -668,10 +709,10 @@ __global__ __launch_bounds__(256, FEW ? 2 : 4) void bwd_gather2_kernel(GatherArg
     for (int r = 0; r < 8; ++r)
 #pragma unroll
         for (int q = 0; q < 8; ++q) acc[r][q] = 0.0f;
-    gather_phase<TG, PH0, PW0, 2, FEW>(a.head[0], a.lv, t, x, acc, sm.h0, stage,
+    gather_phase<TG, PH0, PW0, 2, FEW, ANY>(a.head[0], a.lv, t, x, acc, sm.h0, stage,
                                   SM0::NBUF == 2 ? stage + SM0::GBP : nullptr);
     __syncthreads();   // head 0's LDS is no longer read
-    gather_phase<TG, PH1, PW1, 2, FEW>(a.head[1], a.lv, t, x, acc, sm.h1, stage,
+    gather_phase<TG, PH1, PW1, 2, FEW, ANY>(a.head[1], a.lv, t, x, acc, sm.h1, stage,
                                   SM1::NBUF == 2 ? stage + SM1::GBP : nullptr);
     static_assert(kStage0 >= 4 * 512 && kStage1 >= 4 * 512, "store scratch in the ring");
     __syncthreads();   // the staging ring is free
@@ -683,23 +724,23 @@ bool gather_available(int PH, int PW, int S) {
     return S == 2 && ((PH == 7 && PW == 7) || (PH == 14 && PW == 14));
 }
 
-template <typename TG, bool FEW>
+template <typename TG, bool FEW, bool ANY>
 static void launch_gather_form(const GatherArgs &a, uint32_t g, hipStream_t stream) {
     const bool b0 = a.PH == 7, b1 = a.head[1].PH == 7;
     if (a.nheads == 1) {
-        if (b0) bwd_gather_kernel<TG, 7, 7, 2, false><<<g, 256, 0, stream>>>(a);
-        else bwd_gather_kernel<TG, 14, 14, 2, FEW><<<g, 256, 0, stream>>>(a);
+        if (b0) bwd_gather_kernel<TG, 7, 7, 2, false, ANY><<<g, 256, 0, stream>>>(a);
+        else bwd_gather_kernel<TG, 14, 14, 2, FEW, ANY><<<g, 256, 0, stream>>>(a);
         return;
     }
     constexpr bool few = FEW && sizeof(TG) == 4;   // (gather_few)
     if (b0 && b1)
-        bwd_gather2_kernel<TG, 7, 7, 7, 7, false><<<g, 256, 0, stream>>>(a);
+        bwd_gather2_kernel<TG, 7, 7, 7, 7, false, ANY><<<g, 256, 0, stream>>>(a);
     else if (b0)
-        bwd_gather2_kernel<TG, 7, 7, 14, 14, few><<<g, 256, 0, stream>>>(a);
+        bwd_gather2_kernel<TG, 7, 7, 14, 14, few, ANY><<<g, 256, 0, stream>>>(a);
     else if (b1)
-        bwd_gather2_kernel<TG, 14, 14, 7, 7, few><<<g, 256, 0, stream>>>(a);
+        bwd_gather2_kernel<TG, 14, 14, 7, 7, few, ANY><<<g, 256, 0, stream>>>(a);
     else
-        bwd_gather2_kernel<TG, 14, 14, 14, 14, few><<<g, 256, 0, stream>>>(a);
+        bwd_gather2_kernel<TG, 14, 14, 14, 14, few, ANY><<<g, 256, 0, stream>>>(a);
 }
 
 // A 14x14 grid in few workgroups: the time is the longest tile's chain of RoIs and not the chip's
@@ -727,12 +768,20 @@ hipError_t launch_gather(GatherArgs a, int gout_dtype, hipStream_t stream) {
     const bool few = gather_few(a, gout_dtype, grid);
     // both heads' gradients have one dtype here (the host checks it)
     if (gout_dtype == kF32) {
-        if (few) launch_gather_form<float, true>(a, g, stream);
-        else launch_gather_form<float, false>(a, g, stream);
+        if (few) launch_gather_form<float, true, false>(a, g, stream);
+        else launch_gather_form<float, false, false>(a, g, stream);
         return hipGetLastError();
     }
-    if (few) launch_gather_form<uint16_t, true>(a, g, stream);
-    else launch_gather_form<uint16_t, false>(a, g, stream);
+    bool any = false;   // a head whose RoIs' bytes are not a multiple of 16
+    for (int i = 0; i < a.nheads; ++i)
+        any = any || (static_cast<int64_t>(a.lv.C) * a.head[i].PH * a.head[i].PW) % 8 != 0;
+    if (!any) {
+        if (few) launch_gather_form<uint16_t, true, false>(a, g, stream);
+        else launch_gather_form<uint16_t, false, false>(a, g, stream);
+    } else {
+        if (few) launch_gather_form<uint16_t, true, true>(a, g, stream);
+        else launch_gather_form<uint16_t, false, true>(a, g, stream);
+    }
     return hipGetLastError();
 }
 
