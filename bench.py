@@ -901,7 +901,7 @@ def main_nms(args):
                    "num_boxes": N, "kept": kept},
         "roofline": {"bound": "alu", "achieved": round(achieved, 3), "peak": 157.3,
                      "unit": "TFLOP/s", "frac": round(achieved / 157.3, 5), "traffic": None,
-                     "kernel": "box_nms (sort + overlap masks + scan)", "flops_per_launch": flops,
+                     "kernel": "box_nms (ranks + overlap lists + decisions)", "flops_per_launch": flops,
                      "launch_ms": round(ms, 5)},
         "cpu_baseline": cpu,
         "extra": {"kernel_source_hash": kernel_source_hash()},
